@@ -128,7 +128,10 @@ enum {
 
 /* Schedules for swept_set_tuning. */
 enum {
-    SWEPT_MODE_AUTO = 0,      /* swept stages when the grid can be tiled, else naive */
+    SWEPT_MODE_AUTO = 0,      /* with no tile width and pairs per lane set: the
+                                 register-window schedule (see swept_advance);
+                                 else swept stages when the grid can be tiled,
+                                 else naive */
     SWEPT_MODE_STAGE = 1,     /* swept: one kernel launch per stage (triangle, diamonds) */
     SWEPT_MODE_NAIVE = 2,     /* one launch per time step */
     SWEPT_MODE_STAGE_BANDED = 3, /* swept stages, every diamond on the banded kernel
@@ -165,7 +168,7 @@ int swept_set_tuning(int32_t tile_w, int32_t pairs_per_lane, int32_t mode);
  * How swept_advance, swept_advance_noalloc and swept_advance_batch evaluate
  * SWEPT_HEAT_F64 and SWEPT_HEAT_F32 (the heat sub-timestep of the paper's
  * Section 4).  Both forms give the canonical bits defined above.
- *  - SWEPT_FORM_AUTO (the default): the stage kernels compute
+ *  - SWEPT_FORM_AUTO (the default): the kernels compute
  *    (u[i-1] + u[i+1]) - 2*u[i] as one fused multiply-add,
  *    fma(-2, u[i], u[i-1] + u[i+1]), in the field's precision.  2*u[i] is
  *    exact whenever it is finite, so the subtraction rounds the same exact
@@ -173,13 +176,17 @@ int swept_set_tuning(int32_t tile_w, int32_t pairs_per_lane, int32_t mode);
  *    point instead of five.  The kernels take this form when 0 <= r <= 1/2
  *    (r as rounded to the field's type), the run is at most 1e15 steps
  *    (binary64) or 1e6 steps (binary32), and a check of the initial field on
- *    the device (one extra read of u, enqueued with the stages) finds no
+ *    the device (one extra read of u, enqueued with the stages; the window
+ *    kernel checks the points it holds, each window for itself) finds no
  *    finite |u| above a sixteenth of the type's largest finite value (MAX).
  *    For such r each update is a convex combination of its three inputs, so
  *    no point comes near MAX/2, the only place where the two forms differ
  *    (2*u overflows, the fused form does not); a non-finite value only
  *    produces non-finite values, alike in both forms.  Otherwise the
- *    kernels evaluate the five operations as written.  A batch takes one
+ *    kernels evaluate the five operations as written.  Where r is a power of
+ *    two, the window kernel also fuses the multiply-add u + r*lap in windows
+ *    whose values are large enough that r*lap is exact (three operations).
+ *    A batch takes one
  *    decision for all its heat instances: every one must meet the
  *    conditions (its r, its step count, its field), else all of them run
  *    the five operations; each launch of a batch checks its fields again.
@@ -204,8 +211,9 @@ int swept_set_heat_form(int32_t form);
 int swept_last_heat_form(int32_t *form);
 
 /*
- * Plan the swept run swept_advance would use for these arguments, without
- * running it.  out[0..5] = { tile_w, depth_k, tiles, stages, pairs_per_lane
+ * Plan the swept run for these arguments, without running it: the tiling that
+ * swept_advance uses for the stencils and tunings that run swept stages (the
+ * register-window schedule of automatic calls chooses its windows by itself).  out[0..5] = { tile_w, depth_k, tiles, stages, pairs_per_lane
  * (0 on the lane-frame kernel), mode_used }.  For SWEPT_MODE_STAGE_RAGGED
  * tile_w = 2k is the width of the full tiles and tiles counts the tiles of
  * the ring (the two-fold cover for odd nx).  Returns SWEPT_EINVAL for
@@ -215,7 +223,18 @@ int swept_plan(int64_t nx, int64_t nsteps, int32_t stencil_id, int64_t *out);
 
 /*
  * Advance u (device, nx points of the stencil's type, periodic) by nsteps
- * time steps with the swept rule.  nsteps == 0 is a no-op.  The automatic
+ * time steps.  nsteps == 0 is a no-op.
+ *
+ * Automatic calls (SWEPT_MODE_AUTO, tile width and pairs per lane left at 0) of
+ * the heat stencils run the register-window schedule: stages of many time
+ * steps, each a kernel launch in which every wavefront advances a window of
+ * consecutive points in registers, wide enough that the points it owns depend
+ * on nothing outside it.  Neighbouring windows overlap, so a few per cent of
+ * the updates are computed twice, which costs less than the edges the swept
+ * stages exchange; any nx is taken as it is.  Results are the same bits.  It
+ * takes nx field elements of scratch.
+ *
+ * The other stencils and tunings run the swept rule.  The automatic
  * plan tiles every grid: with equal tiles of the largest even width W that
  * divides nx, up to min(1024, nx/16) points, when W is at least half that
  * target; otherwise (odd nx, or an even nx without such a divisor) with
@@ -233,7 +252,8 @@ int swept_advance(void *u, int64_t nx, int64_t nsteps, int32_t stencil_id,
  * as swept_advance (same arguments, plan, kernels and bits), with the scratch
  * in a fixed array of SWEPT_NOALLOC_SCRATCH_BYTES that the library holds on
  * each GPU it runs on (from swept_init until the process ends) instead of
- * memory it allocates.  The call allocates nothing.  It needs
+ * memory it allocates.  The call allocates nothing.  It is limited to the
+ * sizes whose swept plan fits the array (whichever schedule runs):
  * 3 * nx * (point size) bytes on the swept path with equal tiles (point
  * size: 8 for heat f64, 4 for heat f32, 24 for KS, 72 for Euler; heat f64 up
  * to 5,592,405 points, KS up to 1,864,135), 6 * nx * (point size) + 2 * nx
@@ -369,7 +389,10 @@ int swept_naive_advance_batch(void *const *u, const int64_t *nx, const int64_t *
  * points, and the highest rate in point-steps per second is kept.  Later
  * swept_advance calls of the same stencil with floor(log2 nx) equal to this
  * one's, in SWEPT_MODE_AUTO with tile width and pairs per lane left at 0,
- * use it whenever the chosen width divides their nx.  Results never depend
+ * use it whenever the chosen width divides their nx.  The register-window
+ * schedule is timed as well, over at most 1024 steps of all nx points; where it
+ * is faster than the best of the others those calls run it (the report and
+ * swept_plan then still name the best swept tiling).  Results never depend
  * on the choice.
  *
  * report (host, may be NULL) receives 8 doubles: tau [s], s1 [s], s_full [s],
@@ -405,7 +428,8 @@ int swept_clear_tuning(void);
  * milliseconds (ms_out[i]) and which kernel ran it (kind_out[i]: 0 = banded
  * kernel -- the triangle or a stage capped at the target level, 1 =
  * continuous-band diamond kernel, 2 = lane-frame kernel, 3 = the unequal
- * tiling's kernel, which runs every stage of SWEPT_MODE_STAGE_RAGGED).  At most cap
+ * tiling's kernel, which runs every stage of SWEPT_MODE_STAGE_RAGGED, 4 = the
+ * window kernel).  At most cap
  * entries are written; *count
  * receives the number of stages.  Either output array may be NULL.
  * Returns SWEPT_EINVAL if profiling is off or no swept run was recorded.

@@ -7,7 +7,7 @@ import subprocess
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 SRC = os.path.join(PKG, "csrc", "swept.hip")
-DEPS = [os.path.join(PKG, "csrc", f) for f in ("stencils.hpp", "kernels.hpp")] + \
+DEPS = [os.path.join(PKG, "csrc", f) for f in ("stencils.hpp", "kernels.hpp", "window.hpp")] + \
     [os.path.join(ROOT, "include", h) for h in ("swept.h", "swept_debug.h")]
 LIB = os.path.join(PKG, "libswept.so")
 LIB_COUNT = os.path.join(PKG, "libswept_count.so")
@@ -27,24 +27,28 @@ HIPCC_FLAGS = [
 ]
 
 
-def _compile(out: str, extra, verbose: bool) -> str:
+def _compile(out: str, extra, verbose: bool):
+    """Start compiling into a temporary file; returns (process, tmp, out)."""
     tmp = out + ".tmp%d" % os.getpid()
     cmd = ["hipcc", *HIPCC_FLAGS, *extra, "-I", os.path.join(ROOT, "include"),
            "-I", os.path.join(PKG, "csrc"), SRC, "-o", tmp, *LINK]
     if verbose:
         print(" ".join(cmd), flush=True)
-    subprocess.check_call(cmd)
-    os.replace(tmp, out)
-    return out
+    return subprocess.Popen(cmd), tmp, out
 
 
 def build(verbose: bool = False, counting: bool = True) -> str:
     """Compile csrc/swept.hip into libswept.so next to this file and, with
     counting, the test build libswept_count.so (SWEPT_COUNT_UPDATES: the
-    stage kernels count their point updates)."""
-    _compile(LIB, [], verbose)
+    stage kernels count their point updates), side by side."""
+    jobs = [_compile(LIB, [], verbose)]
     if counting:
-        _compile(LIB_COUNT, ["-DSWEPT_COUNT_UPDATES"], verbose)
+        jobs.append(_compile(LIB_COUNT, ["-DSWEPT_COUNT_UPDATES"], verbose))
+    codes = [p.wait() for p, _, _ in jobs]
+    for (p, tmp, out), rc in zip(jobs, codes):
+        if rc:
+            raise subprocess.CalledProcessError(rc, p.args)
+        os.replace(tmp, out)
     return LIB
 
 

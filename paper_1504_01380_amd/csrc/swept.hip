@@ -22,6 +22,7 @@
 #include "swept.h"
 #include "swept_debug.h"
 #include "kernels.hpp"
+#include "window.hpp"
 
 // Scratch of swept_advance_noalloc: a fixed array that every GPU the library
 // runs on holds until the process ends.  Host code never uses its name as an
@@ -288,6 +289,7 @@ struct Tuned {
     int64_t W;
     int P;                 // pairs per lane; 0: the lane-frame kernel
     bool ragged = false;   // the unequal tiling of depth W/2 (SWEPT_MODE_STAGE_RAGGED)
+    bool window = false;   // the window schedule was faster than this tiling
 };
 std::map<std::pair<int, int>, Tuned> g_tuned;
 // Batch depth per stencil id chosen by swept_autotune_batch (0 = default).
@@ -1629,7 +1631,262 @@ int run_naive_adjoint(const void* u0v, void* gradv, int64_t nx, int64_t nsteps,
     return SWEPT_OK;
 }
 
-// swept_advance after validation: plan, then the swept or the naive schedule
+// ---------------------------------------------------------- register windows
+//
+// The automatic schedule (window.hpp): stages of h time steps from the field to
+// the scratch and back, an even number of them so that the result ends in the
+// caller's field.
+#ifdef SWEPT_COUNT_UPDATES
+// the counting build audits the swept stage kernels: every (point, level) once
+constexpr bool kWindows = false;
+#else
+constexpr bool kWindows = true;
+#endif
+
+bool window_id(int id) { return base_id(id) == SWEPT_HEAT_F64 || base_id(id) == SWEPT_HEAT_F32; }
+
+struct WindowPlan {
+    int M = 0;             // points per lane (0: none)
+    int64_t own = 0;       // points per tile
+    int64_t tiles = 0;
+    int64_t h = 0;         // most time steps of a stage
+    int64_t stages = 0;
+    double cost = 1e300;   // predicted time, ns
+};
+
+// Time of one row (one time step of one window of 64*M points), fitted to
+// sweeps of M and h on MI355X (heat with three operations a point: a lone
+// wave 30 + 4.9 M ns over M = 2..48 at 4096 points; at 2^24 points a SIMD
+// issues 4.4 cycles an operation whatever the number of its waves).
+struct WindowCost {
+    double lat;      // ns a row of a lone wave takes beside its operations
+    double per;      // ns per point and lane
+};
+
+WindowCost window_cost(int id, int ops)
+{
+    return base_id(id) == SWEPT_HEAT_F32 ? WindowCost{30.0, 1.2 * ops} : WindowCost{30.0, 1.63 * ops};
+}
+
+size_t field_bytes(int id);
+
+constexpr int kWindowM[] = {2, 3, 4, 6, 8, 12, 16, 24, 32, 48};
+
+// The window size and stage depth of least predicted time.  A stage costs a
+// launch and its loads and stores (about 2 us, and the field's bytes in and
+// out at 9 TB/s, partly hidden) plus h rows; 1024 SIMDs share the tiles, and
+// a row takes the longer of a lone wave's latency and the issue time of all
+// the waves of a SIMD.  Deep stages spread the launch, wide windows the halo;
+// few tiles (small grids) want small windows, whose rows are short.
+[[maybe_unused]] WindowPlan window_plan(int id, int64_t n, int64_t nsteps, int ops, int64_t hmax)
+{
+    const int R = substeps_of(id);
+    const WindowCost c = window_cost(id, ops);
+    WindowPlan best;
+    for (int M : kWindowM) {
+        const int64_t W = 64 * M;
+        int64_t last = 0;
+        for (int f = 1; f <= 14; ++f) {
+            int64_t h = std::min({W * f / (32 * R), hmax, (nsteps + 1) / 2});
+            if (h < 1 || h == last)
+                continue;
+            last = h;
+            WindowPlan p;
+            p.stages = (nsteps + h - 1) / h;
+            p.stages += p.stages & 1;
+            p.h = (nsteps + p.stages - 1) / p.stages;
+            const int64_t room = W - 2 * R * p.h;
+            p.M = M;
+            p.tiles = (n + room - 1) / room;
+            if (p.tiles > (int64_t(1) << 30))
+                continue;
+            // equal tiles, starting on 64-byte lines where there is room for that
+            p.own = (n + p.tiles - 1) / p.tiles;
+            p.own = std::min(room, (p.own + 15) / 16 * 16);
+            p.tiles = (n + p.own - 1) / p.own;
+            const double w = (double)p.tiles / 1024.0;
+            const double waves = w <= 8.0 ? std::ceil(w) : w + 0.5;
+            const double row = std::max(c.lat + c.per * M, waves * (5.0 + c.per * M));
+            const double mem = (double)n * (double)field_bytes(id) *
+                               (1.0 + (double)W / (double)p.own) / 9000.0;
+            p.cost = (double)p.stages * (2000.0 + mem + (double)p.h * row);
+            if (p.cost < best.cost)
+                best = p;
+        }
+    }
+    return best;
+}
+
+template <class S>
+void launch_window(const WindowArgs<S>& a, int M, hipStream_t st)
+{
+    const dim3 grid((unsigned)((a.tiles + 7) / 8 * 8)), block(64);
+    switch (M) {
+    case 2: hipLaunchKernelGGL((window_kernel<S, 2>), grid, block, 0, st, a); break;
+    case 3: hipLaunchKernelGGL((window_kernel<S, 3>), grid, block, 0, st, a); break;
+    case 4: hipLaunchKernelGGL((window_kernel<S, 4>), grid, block, 0, st, a); break;
+    case 6: hipLaunchKernelGGL((window_kernel<S, 6>), grid, block, 0, st, a); break;
+    case 8: hipLaunchKernelGGL((window_kernel<S, 8>), grid, block, 0, st, a); break;
+    case 12: hipLaunchKernelGGL((window_kernel<S, 12>), grid, block, 0, st, a); break;
+    case 16: hipLaunchKernelGGL((window_kernel<S, 16>), grid, block, 0, st, a); break;
+    case 24: hipLaunchKernelGGL((window_kernel<S, 24>), grid, block, 0, st, a); break;
+    case 32: hipLaunchKernelGGL((window_kernel<S, 32>), grid, block, 0, st, a); break;
+    default: hipLaunchKernelGGL((window_kernel<S, 48>), grid, block, 0, st, a); break;
+    }
+}
+
+// r = 2^-e with e >= 1: e; else 0
+template <class T>
+int pow2_exponent(T r)
+{
+    int e = 0;
+    return r > T(0) && r <= T(0.5) && std::frexp(r, &e) == T(0.5) ? 1 - e : 0;
+}
+
+// The forms a heat call's stages may take: the conditions on r and the run
+// length of range_check, and the exact-product form for r = 2^-e.
+template <class S>
+struct WindowForm {
+    bool fused = false;
+    int e = 0;          // exact-product form for r = 2^-e (0: no)
+    int ops = 5;        // operations per point of the form expected
+    int64_t hmax = int64_t(1) << 40;
+};
+
+template <class S>
+WindowForm<S> window_form(const typename S::Consts& c, int64_t L)
+{
+    WindowForm<S> f;
+    if constexpr (std::is_base_of_v<HeatFma<typename S::T>, S>) {
+        f.ops = 3;
+    } else if constexpr (has_fused_form<S>) {
+        using T = typename S::T;
+        f.fused = g_ctx.heat_form != SWEPT_FORM_CANONICAL && c.r >= 0 && c.r <= 0.5 &&
+                  L <= kFusedMaxLevels<T>;
+        if (f.fused) {
+            f.ops = 4;
+            // a stage of h steps may raise the smallest value allowed to
+            // 2^(emin + e*h): 2^-46 in binary32, 2^-200 in binary64
+            const int room = -(std::numeric_limits<T>::min_exponent - 1) - (sizeof(T) == 8 ? 200 : 46);
+            f.e = pow2_exponent(c.r);
+            if (f.e > 0 && room / f.e >= 16) {
+                f.ops = 3;
+                f.hmax = room / f.e;
+            } else {
+                f.e = 0;
+            }
+        }
+    }
+    return f;
+}
+
+// the record of the last heat call (swept_last_heat_form), and the call's id
+template <class S>
+unsigned long long window_record(const WindowForm<S>& f)
+{
+    if constexpr (!has_fused_form<S>) {
+        return 0;
+    } else {
+        g_ctx.last_batch = false;
+        g_ctx.last_form = f.fused ? SWEPT_FORM_FUSED : SWEPT_FORM_CANONICAL;
+        g_ctx.last_guard = f.fused ? ++g_call_id : 0;
+        return g_ctx.last_guard;
+    }
+}
+
+template <class S>
+int run_window(void* uv, int64_t nx, int64_t nsteps, int id, const typename S::Consts& c)
+{
+    using T = typename S::T;
+    const WindowForm<S> form = window_form<S>(c, nsteps * S::NPHASE);
+    const WindowPlan p = window_plan(id, nx, nsteps, form.ops, form.hmax);
+    if (p.M == 0)
+        return fail(SWEPT_EUNSUPPORTED, "nx = %lld is too long", (long long)nx);
+    int rc = ensure_scratch((size_t)nx * sizeof(T));
+    if (rc)
+        return rc;
+    T* buf[2] = {static_cast<T*>(uv), static_cast<T*>(scratch_base())};
+    const unsigned long long guard = window_record<S>(form);
+    if (g_ctx.profiling) {
+        rc = reserve_events(p.stages);
+        if (rc)
+            return rc;
+        HIP_TRY(hipEventRecord(g_ctx.events[0], g_ctx.stream));
+    }
+    WindowArgs<S> a{};
+    a.n = nx;
+    a.own = p.own;
+    a.tiles = (int)p.tiles;
+    a.c = c;
+    a.fused = form.fused;
+    int64_t done = 0;
+    for (int64_t s = 0; s < p.stages; ++s) {
+        const int64_t next = nsteps / p.stages * (s + 1) + nsteps % p.stages * (s + 1) / p.stages;
+        a.in = buf[s & 1];
+        a.out = buf[(s + 1) & 1];
+        a.steps = (int)(next - done);
+        a.halo = a.steps * S::NPHASE;
+        a.big = std::numeric_limits<T>::max() / (s == 0 ? 16 : 8);
+        a.tiny = form.e > 0 ? std::ldexp(T(1), std::numeric_limits<T>::min_exponent - 1 +
+                                                   form.e * a.steps)
+                            : T(0);
+        a.guard = s == 0 ? guard : 0;
+        done = next;
+        launch_window<S>(a, p.M, g_ctx.stream);
+        if (g_ctx.profiling) {
+            g_ctx.kinds[(size_t)s] = 4;
+            HIP_TRY(hipEventRecord(g_ctx.events[(size_t)s + 1], g_ctx.stream));
+        }
+    }
+    HIP_TRY(hipGetLastError());
+    if (g_ctx.profiling)
+        g_ctx.recorded = p.stages;
+    return SWEPT_OK;
+}
+
+#ifdef SWEPT_COUNT_UPDATES
+int window_dispatch(void*, int64_t, int64_t, int32_t, const double*)
+{
+    return fail(SWEPT_EUNSUPPORTED, "the counting build has no window schedule");
+}
+#else
+int window_dispatch(void* u, int64_t nx, int64_t nsteps, int32_t id, const double* params)
+{
+    switch (id) {
+    case SWEPT_HEAT_F64: return run_window<HeatF64>(u, nx, nsteps, id, heat64_consts(params));
+    case SWEPT_HEAT_F32: return run_window<HeatF32>(u, nx, nsteps, id, heat32_consts(params));
+    case SWEPT_HEAT_F64_FMA: return run_window<HeatFmaF64>(u, nx, nsteps, id, heat64_consts(params));
+    default: return run_window<HeatFmaF32>(u, nx, nsteps, id, heat32_consts(params));
+    }
+}
+#endif
+
+// The scratch the swept or naive schedule of a plan takes (run_swept,
+// run_ragged, run_naive_*): what bounds swept_advance_noalloc's requests.
+size_t plan_scratch(const Plan& p, int64_t nx, int id)
+{
+    const size_t cover = p.ring != nx ? ((size_t)p.ring * field_bytes(id) + 255) / 256 * 256 : 0;
+    switch (p.mode) {
+    case SWEPT_MODE_NAIVE: return (size_t)nx * field_bytes(id);
+    case SWEPT_MODE_STAGE_RAGGED: return cover + 3 * (size_t)p.ring * pt_bytes(id);
+    default: return 3 * (size_t)nx * pt_bytes(id);
+    }
+}
+
+// The window schedule runs every automatic call (no tile width, pairs per lane
+// or mode set) unless swept_autotune measured a swept tiling or the naive
+// schedule to be faster for the stencil and size class.
+bool use_window(int id, int64_t nx)
+{
+    if (!kWindows || !window_id(id) || g_ctx.mode != SWEPT_MODE_AUTO || g_ctx.tile_w != 0 ||
+        g_ctx.ppl != 0)
+        return false;
+    const auto it = g_tuned.find(tune_key(id, nx));
+    return it == g_tuned.end() || it->second.window;
+}
+
+// swept_advance after validation: plan, then the window schedule, or the swept
+// or the naive one where the tuning asks for it
 int advance_dispatch(void* u, int64_t nx, int64_t nsteps, int32_t id, const double* params)
 {
     if (nsteps == 0)
@@ -1638,6 +1895,11 @@ int advance_dispatch(void* u, int64_t nx, int64_t nsteps, int32_t id, const doub
     int rc = make_plan(nx, nsteps, id, &p);
     if (rc)
         return rc;
+    if (use_window(id, nx)) {
+        // swept_advance_noalloc takes the sizes whose swept plan fits its array
+        rc = g_fixed ? ensure_scratch(plan_scratch(p, nx, id)) : SWEPT_OK;
+        return rc ? rc : window_dispatch(u, nx, nsteps, id, params);
+    }
     if (p.mode == SWEPT_MODE_NAIVE) {
         if (id == SWEPT_HEAT_F64 || id == SWEPT_HEAT_F32) {
             g_ctx.last_guard = 0;
@@ -2033,6 +2295,17 @@ int autotune(int64_t nx, int64_t nsteps, int id, const double* params, double* r
                 best_rate = rate;
                 best = Tuned{rg.W, rg.P, true};
             }
+        }
+    }
+    if (kWindows && window_id(id)) {   // the window schedule, over at most 1024 steps
+        const int64_t np = std::min<int64_t>(nsteps, 1024);
+        rc = time_best([&] { return window_dispatch(f.p, nx, np, id, params); }, 3, &t);
+        if (rc)
+            return rc;
+        const double rate = (double)nx * (double)np / t;
+        if (rate > best_rate) {
+            best_rate = rate;
+            best.window = true;
         }
     }
     g_tuned[tune_key(id, nx)] = best;

@@ -1,0 +1,111 @@
+"""The register-window schedule (the automatic schedule of swept_advance)
+against the oracle, bit for bit, where it can go wrong: rings smaller than a
+window (which then holds the ring several times over), owned parts and windows
+that end on, just before or just after the ring's seam, runs of one to a few
+steps (stages of zero steps), every evaluation form of heat and the
+conditions that choose between them."""
+import numpy as np
+import pytest
+
+import workloads
+from tests.conftest import gpu_available, same_bits
+
+pytestmark = [pytest.mark.gpu,
+              pytest.mark.skipif(not gpu_available(), reason="needs a GPU")]
+
+TINY = {np.float64: 2.0 ** -1022, np.float32: 2.0 ** -126}
+
+
+@pytest.fixture(scope="module")
+def sw():
+    import paper_1504_01380_amd as swept
+    swept.init(0)
+    swept.set_tuning(0, 0, swept.MODE_AUTO)
+    swept.clear_tuning()
+    yield swept
+
+
+def run(sw, u0, nsteps, stencil, params):
+    import torch
+    u = torch.from_numpy(np.ascontiguousarray(u0)).to("cuda")
+    sw.advance(u, nsteps, stencil, params)
+    torch.cuda.synchronize()
+    sw.sync()
+    return u.cpu().numpy()
+
+
+def same_up_to_nan(a, b):
+    na, nb = np.isnan(a), np.isnan(b)
+    return np.array_equal(na, nb) and same_bits(a[~na], b[~nb])
+
+
+@pytest.mark.parametrize("dtype", [np.float64, np.float32])
+@pytest.mark.parametrize("r", [0.25, 0.3, 0.5, 0.6])
+@pytest.mark.parametrize("n,nsteps", [
+    (3, 1), (3, 2), (5, 7), (31, 64), (64, 129), (127, 1), (128, 3), (257, 200), (1000, 100),
+    (4095, 301), (4096, 1), (4097, 777), (65536 + 48, 150), (300000, 97), (1 << 20, 33),
+])
+def test_heat_bitwise(sw, oracle_mod, n, nsteps, r, dtype):
+    """r = 1/4 and 1/2: the exact-product form; 0.3: the fused Laplacian;
+    0.6: the operations as written."""
+    u0 = workloads.white_noise(n, seed=n + nsteps, dtype=dtype)
+    got = run(sw, u0, nsteps, "heat", [r])
+    assert sw.last_heat_form() == (sw.FORM_FUSED if r <= 0.5 else sw.FORM_CANONICAL)
+    assert same_up_to_nan(got, oracle_mod.heat(u0, nsteps, r))
+
+
+@pytest.mark.parametrize("dtype", [np.float64, np.float32])
+def test_heat_tiny_values(sw, oracle_mod, dtype):
+    """Values down to the subnormals: products r*lap underflow, so a window
+    that holds one must not take the exact-product form; zeros may."""
+    n, nsteps = 5000, 300
+    u0 = workloads.white_noise(n, seed=3, dtype=dtype)
+    u0[1000:1400] = (u0[1000:1400] * 4 * TINY[dtype]).astype(dtype)
+    u0[3000:3500] = 0
+    got = run(sw, u0, nsteps, "heat", [0.25])
+    assert sw.last_heat_form() == sw.FORM_FUSED
+    assert same_bits(got, oracle_mod.heat(u0, nsteps, 0.25))
+    small = (workloads.white_noise(n, seed=4, dtype=dtype) * 8 * TINY[dtype]).astype(dtype)
+    assert same_bits(run(sw, small, 40, "heat", [0.25]), oracle_mod.heat(small, 40, 0.25))
+
+
+@pytest.mark.parametrize("dtype", [np.float64, np.float32])
+def test_heat_range_check(sw, oracle_mod, dtype):
+    """A value above MAX/16 sends its windows to the operations as written and
+    is reported; values of 0.4..0.6 MAX overflow there as in the oracle; the
+    next call is fused again."""
+    big = np.finfo(dtype).max
+    u0 = workloads.white_noise(6001, seed=9, dtype=dtype)
+    lim = dtype(big / 16)
+    for at, form in ((lim, sw.FORM_FUSED), (np.nextafter(lim, dtype(np.inf)), sw.FORM_CANONICAL),
+                     (dtype(0.55) * big, sw.FORM_CANONICAL), (dtype(np.inf), sw.FORM_FUSED),
+                     (dtype(1), sw.FORM_FUSED)):
+        v = u0.copy()
+        v[2500:2503] = at
+        got = run(sw, v, 90, "heat", [0.25])
+        assert sw.last_heat_form() == form
+        assert same_up_to_nan(got, oracle_mod.heat(v, 90, 0.25))
+
+
+@pytest.mark.parametrize("dtype", [np.float64, np.float32])
+@pytest.mark.parametrize("n,nsteps", [(7, 5), (999, 250), (70001, 60)])
+def test_heat_fma_bitwise(sw, oracle_mod, n, nsteps, dtype):
+    u0 = workloads.white_noise(n, seed=n, dtype=dtype)
+    assert same_bits(run(sw, u0, nsteps, "heat_fma", [0.3]), oracle_mod.heat_fma(u0, nsteps, 0.3))
+
+
+@pytest.mark.parametrize("n,W", [(4096, 128), (65536, 1024)])
+def test_profiled_stages_are_reported(sw, n, W):
+    import torch
+    u = torch.from_numpy(workloads.white_noise(n, seed=1)).cuda()
+    sw.set_profiling(True)
+    try:
+        sw.advance(u, 500, "heat", [0.25])
+        ms, kind = sw.stage_times()
+        assert set(kind) == {4} and len(kind) % 2 == 0 and min(ms) > 0
+        sw.set_tuning(W, 0, sw.MODE_AUTO)      # a tile width asks for the swept stages
+        sw.advance(u, 500, "heat", [0.25])
+        assert 4 not in sw.stage_times()[1]
+    finally:
+        sw.set_tuning(0, 0, sw.MODE_AUTO)
+        sw.set_profiling(False)
