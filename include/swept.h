@@ -226,7 +226,7 @@ int swept_plan(int64_t nx, int64_t nsteps, int32_t stencil_id, int64_t *out);
  * time steps.  nsteps == 0 is a no-op.
  *
  * Automatic calls (SWEPT_MODE_AUTO, tile width and pairs per lane left at 0) of
- * the heat stencils run the register-window schedule: stages of many time
+ * the heat and KS stencils run the register-window schedule: stages of many time
  * steps, each a kernel launch in which every wavefront advances a window of
  * consecutive points in registers, wide enough that the points it owns depend
  * on nothing outside it.  Neighbouring windows overlap, so a few per cent of

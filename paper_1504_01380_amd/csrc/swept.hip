@@ -1643,7 +1643,7 @@ constexpr bool kWindows = false;
 constexpr bool kWindows = true;
 #endif
 
-bool window_id(int id) { return base_id(id) == SWEPT_HEAT_F64 || base_id(id) == SWEPT_HEAT_F32; }
+bool window_id(int id) { return id != SWEPT_EULER_F64; }
 
 struct WindowPlan {
     int M = 0;             // points per lane (0: none)
@@ -1665,12 +1665,18 @@ struct WindowCost {
 
 WindowCost window_cost(int id, int ops)
 {
-    return base_id(id) == SWEPT_HEAT_F32 ? WindowCost{30.0, 1.2 * ops} : WindowCost{30.0, 1.63 * ops};
+    switch (base_id(id)) {
+    case SWEPT_HEAT_F32: return WindowCost{30.0, 1.2 * ops};
+    case SWEPT_KS_F64: return WindowCost{90.0, 1.63 * ops};
+    default: return WindowCost{30.0, 1.63 * ops};
+    }
 }
 
 size_t field_bytes(int id);
 
-constexpr int kWindowM[] = {2, 3, 4, 6, 8, 12, 16, 24, 32, 48};
+// points per lane the window kernels are built for
+constexpr int kWindowHeat[] = {2, 3, 4, 6, 8, 12, 16, 24, 32, 48};
+constexpr int kWindowKs[] = {2, 3, 4, 6, 8, 10, 12, 14, 16, 18, 20, 24};
 
 // The window size and stage depth of least predicted time.  A stage costs a
 // launch and its loads and stores (about 2 us, and the field's bytes in and
@@ -1683,7 +1689,11 @@ constexpr int kWindowM[] = {2, 3, 4, 6, 8, 12, 16, 24, 32, 48};
     const int R = substeps_of(id);
     const WindowCost c = window_cost(id, ops);
     WindowPlan best;
-    for (int M : kWindowM) {
+    const bool ks = base_id(id) == SWEPT_KS_F64;
+    const int* sizes = ks ? kWindowKs : kWindowHeat;
+    const int nsizes = (int)(ks ? std::size(kWindowKs) : std::size(kWindowHeat));
+    for (int i = 0; i < nsizes; ++i) {
+        const int M = sizes[i];
         const int64_t W = 64 * M;
         int64_t last = 0;
         for (int f = 1; f <= 14; ++f) {
@@ -1717,22 +1727,26 @@ constexpr int kWindowM[] = {2, 3, 4, 6, 8, 12, 16, 24, 32, 48};
     return best;
 }
 
+template <class S, int... MS>
+void launch_window_of(const WindowArgs<S>& a, int M, hipStream_t st, std::integer_sequence<int, MS...>)
+{
+    const dim3 grid((unsigned)((a.tiles + 7) / 8 * 8)), block(64);
+    auto one = [&](auto m) {
+        constexpr int MM = decltype(m)::value;
+        if (M == MM)
+            hipLaunchKernelGGL((window_kernel<S, MM>), grid, block, 0, st, a);
+    };
+    (one(std::integral_constant<int, MS>{}), ...);
+}
+
+// the sizes of kWindowHeat and kWindowKs
 template <class S>
 void launch_window(const WindowArgs<S>& a, int M, hipStream_t st)
 {
-    const dim3 grid((unsigned)((a.tiles + 7) / 8 * 8)), block(64);
-    switch (M) {
-    case 2: hipLaunchKernelGGL((window_kernel<S, 2>), grid, block, 0, st, a); break;
-    case 3: hipLaunchKernelGGL((window_kernel<S, 3>), grid, block, 0, st, a); break;
-    case 4: hipLaunchKernelGGL((window_kernel<S, 4>), grid, block, 0, st, a); break;
-    case 6: hipLaunchKernelGGL((window_kernel<S, 6>), grid, block, 0, st, a); break;
-    case 8: hipLaunchKernelGGL((window_kernel<S, 8>), grid, block, 0, st, a); break;
-    case 12: hipLaunchKernelGGL((window_kernel<S, 12>), grid, block, 0, st, a); break;
-    case 16: hipLaunchKernelGGL((window_kernel<S, 16>), grid, block, 0, st, a); break;
-    case 24: hipLaunchKernelGGL((window_kernel<S, 24>), grid, block, 0, st, a); break;
-    case 32: hipLaunchKernelGGL((window_kernel<S, 32>), grid, block, 0, st, a); break;
-    default: hipLaunchKernelGGL((window_kernel<S, 48>), grid, block, 0, st, a); break;
-    }
+    if constexpr (is_ks<S>)
+        launch_window_of<S>(a, M, st, std::integer_sequence<int, 2, 3, 4, 6, 8, 10, 12, 14, 16, 18, 20, 24>{});
+    else
+        launch_window_of<S>(a, M, st, std::integer_sequence<int, 2, 3, 4, 6, 8, 12, 16, 24, 32, 48>{});
 }
 
 // r = 2^-e with e >= 1: e; else 0
@@ -1743,12 +1757,14 @@ int pow2_exponent(T r)
     return r > T(0) && r <= T(0.5) && std::frexp(r, &e) == T(0.5) ? 1 - e : 0;
 }
 
-// The forms a heat call's stages may take: the conditions on r and the run
-// length of range_check, and the exact-product form for r = 2^-e.
+// The forms a call's stages may take.  Heat: the conditions on r and the run
+// length of range_check, and the exact-product form for r = 2^-e.  KS: the
+// conditions on the constants (at kKsLap and kKsExact).
 template <class S>
 struct WindowForm {
     bool fused = false;
-    int e = 0;          // exact-product form for r = 2^-e (0: no)
+    int e = 0;          // heat: exact-product form for r = 2^-e (0: no)
+    bool exact = false; // KS: exact-product form
     int ops = 5;        // operations per point of the form expected
     int64_t hmax = int64_t(1) << 40;
 };
@@ -1757,7 +1773,17 @@ template <class S>
 WindowForm<S> window_form(const typename S::Consts& c, int64_t L)
 {
     WindowForm<S> f;
-    if constexpr (std::is_base_of_v<HeatFma<typename S::T>, S>) {
+    if constexpr (is_ks<S>) {
+        auto pow2 = [](double x, int lo, int hi) {
+            int e = 0;
+            return std::frexp(x, &e) == 0.5 && e - 1 >= lo && e - 1 <= hi;
+        };
+        constexpr bool fma = is_ks_fma<S>;
+        const bool moderate = std::max({std::fabs(c.dt), std::fabs(c.h), c.c1, c.c2}) <= 1e10;
+        f.exact = moderate && pow2(c.c2, 0, 8) && pow2(c.c1, -8, 8);
+        f.fused = fma ? f.exact : moderate;
+        f.ops = fma ? (f.exact ? 18 : 22) : (f.exact ? 21 : (f.fused ? 27 : 30));
+    } else if constexpr (std::is_base_of_v<HeatFma<typename S::T>, S>) {
         f.ops = 3;
     } else if constexpr (has_fused_form<S>) {
         using T = typename S::T;
@@ -1826,10 +1852,15 @@ int run_window(void* uv, int64_t nx, int64_t nsteps, int id, const typename S::C
         a.out = buf[(s + 1) & 1];
         a.steps = (int)(next - done);
         a.halo = a.steps * S::NPHASE;
-        a.big = std::numeric_limits<T>::max() / (s == 0 ? 16 : 8);
-        a.tiny = form.e > 0 ? std::ldexp(T(1), std::numeric_limits<T>::min_exponent - 1 +
-                                                   form.e * a.steps)
-                            : T(0);
+        if constexpr (is_ks<S>) {
+            a.big = 1e30;
+            a.tiny = form.exact ? std::ldexp(1.0, -400) : 0.0;
+        } else {
+            a.big = std::numeric_limits<T>::max() / (s == 0 ? 16 : 8);
+            a.tiny = form.e > 0 ? std::ldexp(T(1), std::numeric_limits<T>::min_exponent - 1 +
+                                                       form.e * a.steps)
+                                : T(0);
+        }
         a.guard = s == 0 ? guard : 0;
         done = next;
         launch_window<S>(a, p.M, g_ctx.stream);
@@ -1856,6 +1887,8 @@ int window_dispatch(void* u, int64_t nx, int64_t nsteps, int32_t id, const doubl
     case SWEPT_HEAT_F64: return run_window<HeatF64>(u, nx, nsteps, id, heat64_consts(params));
     case SWEPT_HEAT_F32: return run_window<HeatF32>(u, nx, nsteps, id, heat32_consts(params));
     case SWEPT_HEAT_F64_FMA: return run_window<HeatFmaF64>(u, nx, nsteps, id, heat64_consts(params));
+    case SWEPT_KS_F64: return run_window<KSF64>(u, nx, nsteps, id, ks_consts(params));
+    case SWEPT_KS_F64_FMA: return run_window<KSFmaF64>(u, nx, nsteps, id, ks_consts(params));
     default: return run_window<HeatFmaF32>(u, nx, nsteps, id, heat32_consts(params));
     }
 }

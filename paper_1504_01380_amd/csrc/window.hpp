@@ -41,11 +41,12 @@ struct WindowArgs {
     int halo;        // points on either side of them
     int steps;       // time steps of this stage
     typename S::Consts c;
-    // heat: the forms this stage may take (window_form) and their conditions
-    typename S::T big;          // largest finite |u| of the fused forms
-    typename S::T tiny;         // smallest nonzero |u| of the exact-product form (0: not allowed)
-    unsigned long long guard;   // the call's id on its first stage (marks the call), else 0
-    int fused;                  // 0: the canonical form only
+    // the evaluation forms this stage may take and their conditions on the
+    // values of a window (heat: window_advance; KS: ks_advance)
+    int fused;                  // 0: the operations as written only
+    typename S::T big;          // largest |u| of the fused forms
+    typename S::T tiny;         // smallest |u| of the exact-product form (0: not allowed)
+    unsigned long long guard;   // heat: the call's id on its first stage (marks the call), else 0
 };
 
 // heat: the fused Laplacian (HeatLap) where r is a power of two, r = 2^-e.
@@ -133,6 +134,183 @@ __device__ __forceinline__ void window_advance(typename S::T (&u)[M], const Wind
     heat_rows<S, M>(u, g.steps, g.c);
 }
 
+// ------------------------------------------------------------------- KS
+// Three evaluations of the KS step with the same bits.
+//  kKsWritten  the operations as written (30 a point and step; 22 on KSFmaF64).
+//  kKsLap      D2's (l + r) - 2c as fma(-2, c, l + r), as in HeatLap (26).
+//              Needs |a| <= MAX/2 for every a that D2 is applied to.
+//  kKsExact    for c1 = 1/(2dx) and c2 = 1/dx^2 powers of two: multiplications
+//              by them are exact, so they move into the operation that takes
+//              the product (fma), and b = D2(a) is kept as b/c2, which saves
+//              its multiplication (20; KSFmaF64 18).  With X = -F(a, b) and
+//              B = b/c2: X/c2 = (a*(ra - la)*(c1/c2) + B) + D2(B), every
+//              operation the written one scaled by a power of two.  Needs no
+//              underflow: a scaled result below the smallest normal number
+//              would round where the written one does not.
+// Both hold for a whole step if 2^-400 <= |u| <= 1e30 at its start and the
+// constants are moderate (window_form: all at most 1e10, and for kKsExact
+// c2 in [1, 2^8], c1 in [2^-8, 2^8]).  From above: |w| <= 4e40, |F| <= 3e70,
+// |v| <= 3e80, |z| <= 2e91, |F| <= 2e171, |u'| <= 2e181.  From below, by
+// the units the values are multiples of (rounding never makes one finer): u of
+// 2^-452, and so is u[i+1] - u[i-1], so a product of two is 0 or at least
+// 2^-852; v = u - h*X is 0 or at least 2^-54 |u| (what cancellation leaves is
+// half a unit of u or more), so a multiple of 2^-506, and a product of v and
+// a difference of two v is 0 or at least 2^-960, a multiple of 2^-1012.
+// Divided by the powers of two above that is a multiple of 2^-1036, so every
+// scaled sum is exact where the smallest subnormal, 2^-1074, could matter.
+// So the wave checks u at every step of a stage: the largest and the smallest
+// magnitude of all points' high words, compared as binary32 bit patterns (a
+// high word's top bits order like the number; patterns of binary32 NaNs start
+// at 2^1017, which a step that starts below 1e30 cannot reach): one v_max3 and
+// one v_min3 per two points.  A window that leaves the range is loaded again
+// and runs the stage as written (its input is intact: stages go from one
+// buffer to the other).
+enum { kKsWritten = 0, kKsLap = 1, kKsExact = 2 };
+
+template <class S>
+constexpr bool is_ks = std::is_base_of_v<KSF64, S>;
+template <class S>
+constexpr bool is_ks_fma = std::is_base_of_v<KSFmaF64, S>;
+
+// One Runge-Kutta half of a step for all points: out = u + coef*F(a, D2(a))
+// (out may be u)
+template <class S, int FORM, int M>
+__device__ __forceinline__ void ks_half(const double (&a)[M], const double (&u)[M],
+                                        double (&out)[M], double coef, const KSF64::Consts& k,
+                                        double c1s)
+{
+    constexpr bool kFma = is_ks_fma<S>;
+    auto lap = [](double l, double c, double r) {
+        if constexpr (FORM == kKsWritten && !kFma)
+            return (l + r) - 2.0 * c;
+        else
+            return fmad(-2.0, c, l + r);
+    };
+    double b[M];
+    {
+        const double la = dpp_record<kWaveShr1>(a[M - 1]), ra = dpp_record<kWaveShl1>(a[0]);
+#pragma unroll
+        for (int q = 0; q < M; ++q) {
+            b[q] = lap(q > 0 ? a[q > 0 ? q - 1 : 0] : la, a[q],
+                       q + 1 < M ? a[q + 1 < M ? q + 1 : 0] : ra);
+            if constexpr (FORM != kKsExact)
+                b[q] = b[q] * k.c2;
+        }
+        const double lb = dpp_record<kWaveShr1>(b[M - 1]), rb = dpp_record<kWaveShl1>(b[0]);
+#pragma unroll
+        for (int q = 0; q < M; ++q) {
+            const double al = q > 0 ? a[q > 0 ? q - 1 : 0] : la;
+            const double ar = q + 1 < M ? a[q + 1 < M ? q + 1 : 0] : ra;
+            const double bl = q > 0 ? b[q > 0 ? q - 1 : 0] : lb;
+            const double br = q + 1 < M ? b[q + 1 < M ? q + 1 : 0] : rb;
+            const double d2 = lap(bl, b[q], br);
+            if constexpr (FORM == kKsExact) {
+                // c1s = c1/c2, coef = h*c2 or dt*c2
+                double t;
+                if constexpr (kFma)
+                    t = fmad(a[q], (ar - al) * c1s, b[q]);
+                else
+                    t = fmad(a[q] * (ar - al), c1s, b[q]);
+                const double x = fmad(d2, k.c2, t);
+                out[q] = kFma ? fmad(-coef, x, u[q]) : u[q] - coef * x;
+            } else {
+                const double d1 = (ar - al) * k.c1;
+                const double t = kFma ? fmad(a[q], d1, b[q]) : a[q] * d1 + b[q];
+                const double f = -(t + d2 * k.c2);
+                out[q] = kFma ? fmad(coef, f, u[q]) : u[q] + coef * f;
+            }
+        }
+    }
+}
+
+// `steps` KS steps of the window; returns (kKsLap, kKsExact) whether every
+// step's u stayed in the form's range
+template <class S, int FORM, int M>
+__device__ __forceinline__ bool ks_rows(double (&u)[M], int steps, const KSF64::Consts& k)
+{
+    const double c1s = k.c1 / k.c2;   // exact where it is used (kKsExact)
+    const double ch = FORM == kKsExact ? k.h * k.c2 : k.h;
+    const double cf = FORM == kKsExact ? k.dt * k.c2 : k.dt;
+    float hi = 0.0f, lo = __int_as_float(0x7f7fffff);
+    double v[M];
+    for (int s = 0; s < steps; ++s) {
+        ks_half<S, FORM, M>(u, u, v, ch, k, c1s);
+        ks_half<S, FORM, M>(v, u, u, cf, k, c1s);
+        if constexpr (FORM != kKsWritten) {
+#pragma unroll
+            for (int q = 0; q < M; q += 2) {
+                const int x = __double2hiint(u[q]), y = __double2hiint(u[q + 1 < M ? q + 1 : q]);
+                asm("v_max3_f32 %0, %0, |%1|, |%2|" : "+v"(hi) : "v"(x), "v"(y));
+                if constexpr (FORM == kKsExact)
+                    asm("v_min3_f32 %0, %0, |%1|, |%2|" : "+v"(lo) : "v"(x), "v"(y));
+            }
+        }
+    }
+    if constexpr (FORM == kKsWritten)
+        return true;
+    // high words: 1e30 = 0x46293e59..., 2^-400 = 0x26f00000
+    const bool ok = hi < __int_as_float(0x46293e59) &&
+                    (FORM != kKsExact || lo > __int_as_float(0x26f00000));
+    return __all(ok);
+}
+
+// A lane's M points of the window that starts at point x0 of the ring
+// (-n < x0 < n where n >= 64*M).
+template <class T, int M>
+__device__ __forceinline__ void window_load(T (&u)[M], const T* in, int64_t n, int64_t x0)
+{
+    constexpr int W = 64 * M;
+    const int lane = threadIdx.x;
+    if (x0 >= 0 && x0 + W <= n) {
+        const T* p = in + (x0 + lane * M);
+#pragma unroll
+        for (int q = 0; q < M; ++q)
+            u[q] = p[q];
+    } else {   // the window crosses the ring's seam, perhaps more than once
+        int64_t x = x0 + lane * M;
+        if (n >= W) {
+            x = x < 0 ? x + n : (x >= n ? x - n : x);
+        } else {
+            const int y = (int)x % (int)n;
+            x = y < 0 ? y + n : y;
+        }
+#pragma unroll
+        for (int q = 0; q < M; ++q) {
+            u[q] = in[x];
+            x = x + 1 == n ? 0 : x + 1;
+        }
+    }
+}
+
+// A KS stage of the window: the cheapest form its values allow, and the
+// operations as written where a value leaves the form's range on the way.
+template <class S, int M>
+__device__ __forceinline__ void ks_advance(double (&u)[M], const WindowArgs<S>& g, int64_t x0)
+{
+    if (g.fused != 0) {
+        bool in = true, small = g.tiny == 0.0;
+#pragma unroll
+        for (int q = 0; q < M; ++q) {
+            const double a = __builtin_fabs(u[q]);
+            in = in && a <= g.big;
+            small = small || !(a >= g.tiny);
+        }
+        if (__all(in)) {
+            bool ok;
+            if (!__any(small))
+                ok = ks_rows<S, kKsExact, M>(u, g.steps, g.c);
+            else if constexpr (!is_ks_fma<S>)
+                ok = ks_rows<S, kKsLap, M>(u, g.steps, g.c);
+            else
+                ok = ks_rows<S, kKsWritten, M>(u, g.steps, g.c);
+            if (ok)
+                return;
+            window_load<double, M>(u, g.in, g.n, x0);
+        }
+    }
+    ks_rows<S, kKsWritten, M>(u, g.steps, g.c);
+}
+
 // One stage: workgroup = one wave = one tile.  Consecutive tiles go to the
 // same XCD (workgroups are dealt to the eight XCDs in turn), so that the
 // halos neighbouring tiles share are read through one L2.
@@ -140,7 +318,6 @@ template <class S, int M>
 __global__ __launch_bounds__(64) void window_kernel(WindowArgs<S> g)
 {
     using T = typename S::T;
-    constexpr int W = 64 * M;
     const int lane = threadIdx.x;
     const unsigned per = (unsigned)(g.tiles + 7) / 8;
     const unsigned tile = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
@@ -149,27 +326,11 @@ __global__ __launch_bounds__(64) void window_kernel(WindowArgs<S> g)
     const int64_t t0 = (int64_t)tile * g.own;
     const int64_t x0 = t0 - g.halo;
     T u[M];
-    if (x0 >= 0 && x0 + W <= g.n) {
-        const T* p = g.in + (x0 + lane * M);
-#pragma unroll
-        for (int q = 0; q < M; ++q)
-            u[q] = p[q];
-    } else {   // the window crosses the ring's seam, perhaps more than once
-        int64_t x = x0 + lane * M;
-        if (g.n >= W) {
-            x = x < 0 ? x + g.n : (x >= g.n ? x - g.n : x);
-        } else {
-            const int n = (int)g.n;
-            const int y = (int)x % n;
-            x = y < 0 ? y + n : y;
-        }
-#pragma unroll
-        for (int q = 0; q < M; ++q) {
-            u[q] = g.in[x];
-            x = x + 1 == g.n ? 0 : x + 1;
-        }
-    }
-    window_advance<S, M>(u, g);
+    window_load<T, M>(u, g.in, g.n, x0);
+    if constexpr (is_ks<S>)
+        ks_advance<S, M>(u, g, x0);
+    else
+        window_advance<S, M>(u, g);
     const int64_t left = g.n - t0;
     const int cnt = (int)(left < g.own ? left : g.own);
     const int c0 = lane * M - g.halo;   // this lane's first column among the owned points

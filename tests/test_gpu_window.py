@@ -94,6 +94,53 @@ def test_heat_fma_bitwise(sw, oracle_mod, n, nsteps, dtype):
     assert same_bits(run(sw, u0, nsteps, "heat_fma", [0.3]), oracle_mod.heat_fma(u0, nsteps, 0.3))
 
 
+KS_P = [workloads.KS_DT, workloads.KS_DX]
+
+
+@pytest.mark.parametrize("fma", [False, True])
+@pytest.mark.parametrize("par", [KS_P, [0.005, 0.7], [1e-4, 0.25]])
+@pytest.mark.parametrize("n,nsteps", [
+    (3, 1), (3, 2), (5, 7), (33, 20), (127, 3), (128, 1), (257, 55), (1000, 100), (4097, 64),
+    (65536 + 16, 41), (300000, 30), (1 << 20, 9),
+])
+def test_ks_bitwise(sw, oracle_mod, n, nsteps, par, fma):
+    """dx = 1/2 and 1/4: the exact-product form (1/dx^2 a power of two); 0.7:
+    the fused Laplacian."""
+    u0 = workloads.smoothed_noise(n, seed=n + nsteps)
+    got = run(sw, u0, nsteps, "ks_fma" if fma else "ks", par)
+    want = (oracle_mod.ks_fma if fma else oracle_mod.ks)(u0, nsteps, *par)
+    assert same_bits(got, want)
+
+
+@pytest.mark.parametrize("fma", [False, True])
+@pytest.mark.parametrize("par", [KS_P, [0.005, 0.7]])
+def test_ks_leaves_the_fused_range(sw, oracle_mod, par, fma):
+    """Zeros, subnormals and a localised pulse whose tails underflow as they
+    spread (below the exact-product form's range), values that start above
+    1e30, and a run that grows past it inside a stage and overflows: each as
+    the oracle computes it."""
+    oracle = oracle_mod.ks_fma if fma else oracle_mod.ks
+    name = "ks_fma" if fma else "ks"
+    n = 3000
+    zero = np.zeros(n)
+    pulse = zero.copy()
+    pulse[1500:1520] = 0.3
+    mixed = workloads.smoothed_noise(n, seed=2)
+    mixed[700:900] *= 2.0 ** -1015
+    mixed[1200:1210] = 0.0
+    huge = workloads.smoothed_noise(n, seed=3)
+    huge[50] = 3e200
+    growing = workloads.smoothed_noise(n, seed=4)
+    growing[2000:2003] = [3e3, -2e3, 5e3]
+    inf = workloads.smoothed_noise(n, seed=5)
+    inf[10] = np.inf
+    for u0, nsteps in ((zero, 20), (pulse, 260), (mixed, 90), (huge, 6), (growing, 12),
+                       (growing, 40), (inf, 5)):
+        want = oracle(u0, nsteps, *par)
+        assert same_up_to_nan(run(sw, u0, nsteps, name, par), want)
+    assert not np.all(np.isfinite(oracle(growing, 40, *par)))   # the case does leave the range
+
+
 @pytest.mark.parametrize("n,W", [(4096, 128), (65536, 1024)])
 def test_profiled_stages_are_reported(sw, n, W):
     import torch
