@@ -212,7 +212,7 @@ int swept_last_heat_form(int32_t *form);
 
 /*
  * Plan the swept run for these arguments, without running it: the tiling that
- * swept_advance uses for the stencils and tunings that run swept stages (the
+ * swept_advance uses for the tunings that run swept stages (the
  * register-window schedule of automatic calls chooses its windows by itself).  out[0..5] = { tile_w, depth_k, tiles, stages, pairs_per_lane
  * (0 on the lane-frame kernel), mode_used }.  For SWEPT_MODE_STAGE_RAGGED
  * tile_w = 2k is the width of the full tiles and tiles counts the tiles of
@@ -225,8 +225,8 @@ int swept_plan(int64_t nx, int64_t nsteps, int32_t stencil_id, int64_t *out);
  * Advance u (device, nx points of the stencil's type, periodic) by nsteps
  * time steps.  nsteps == 0 is a no-op.
  *
- * Automatic calls (SWEPT_MODE_AUTO, tile width and pairs per lane left at 0) of
- * the heat and KS stencils run the register-window schedule: stages of many time
+ * Automatic calls (SWEPT_MODE_AUTO, tile width and pairs per lane left at 0)
+ * run the register-window schedule: stages of many time
  * steps, each a kernel launch in which every wavefront advances a window of
  * consecutive points in registers, wide enough that the points it owns depend
  * on nothing outside it.  Neighbouring windows overlap, so a few per cent of
@@ -234,7 +234,7 @@ int swept_plan(int64_t nx, int64_t nsteps, int32_t stencil_id, int64_t *out);
  * stages exchange; any nx is taken as it is.  Results are the same bits.  It
  * takes nx field elements of scratch.
  *
- * The other stencils and tunings run the swept rule.  The automatic
+ * Other tunings run the swept rule.  Its automatic
  * plan tiles every grid: with equal tiles of the largest even width W that
  * divides nx, up to min(1024, nx/16) points, when W is at least half that
  * target; otherwise (odd nx, or an even nx without such a divisor) with

@@ -1643,8 +1643,6 @@ constexpr bool kWindows = false;
 constexpr bool kWindows = true;
 #endif
 
-bool window_id(int id) { return id != SWEPT_EULER_F64; }
-
 struct WindowPlan {
     int M = 0;             // points per lane (0: none)
     int64_t own = 0;       // points per tile
@@ -1668,6 +1666,7 @@ WindowCost window_cost(int id, int ops)
     switch (base_id(id)) {
     case SWEPT_HEAT_F32: return WindowCost{30.0, 1.2 * ops};
     case SWEPT_KS_F64: return WindowCost{90.0, 1.63 * ops};
+    case SWEPT_EULER_F64: return WindowCost{150.0, 1.75 * ops};
     default: return WindowCost{30.0, 1.63 * ops};
     }
 }
@@ -1677,6 +1676,7 @@ size_t field_bytes(int id);
 // points per lane the window kernels are built for
 constexpr int kWindowHeat[] = {2, 3, 4, 6, 8, 12, 16, 24, 32, 48};
 constexpr int kWindowKs[] = {2, 3, 4, 6, 8, 10, 12, 14, 16, 18, 20, 24};
+constexpr int kWindowEuler[] = {1, 2, 3, 4, 6};
 
 // The window size and stage depth of least predicted time.  A stage costs a
 // launch and its loads and stores (about 2 us, and the field's bytes in and
@@ -1689,9 +1689,15 @@ constexpr int kWindowKs[] = {2, 3, 4, 6, 8, 10, 12, 14, 16, 18, 20, 24};
     const int R = substeps_of(id);
     const WindowCost c = window_cost(id, ops);
     WindowPlan best;
-    const bool ks = base_id(id) == SWEPT_KS_F64;
-    const int* sizes = ks ? kWindowKs : kWindowHeat;
-    const int nsizes = (int)(ks ? std::size(kWindowKs) : std::size(kWindowHeat));
+    const int* sizes = kWindowHeat;
+    int nsizes = (int)std::size(kWindowHeat);
+    if (base_id(id) == SWEPT_KS_F64) {
+        sizes = kWindowKs;
+        nsizes = (int)std::size(kWindowKs);
+    } else if (id == SWEPT_EULER_F64) {
+        sizes = kWindowEuler;
+        nsizes = (int)std::size(kWindowEuler);
+    }
     for (int i = 0; i < nsizes; ++i) {
         const int M = sizes[i];
         const int64_t W = 64 * M;
@@ -1739,12 +1745,14 @@ void launch_window_of(const WindowArgs<S>& a, int M, hipStream_t st, std::intege
     (one(std::integral_constant<int, MS>{}), ...);
 }
 
-// the sizes of kWindowHeat and kWindowKs
+// the sizes of kWindowHeat, kWindowKs and kWindowEuler
 template <class S>
 void launch_window(const WindowArgs<S>& a, int M, hipStream_t st)
 {
     if constexpr (is_ks<S>)
         launch_window_of<S>(a, M, st, std::integer_sequence<int, 2, 3, 4, 6, 8, 10, 12, 14, 16, 18, 20, 24>{});
+    else if constexpr (has_faces<S>::value)
+        launch_window_of<S>(a, M, st, std::integer_sequence<int, 1, 2, 3, 4, 6>{});
     else
         launch_window_of<S>(a, M, st, std::integer_sequence<int, 2, 3, 4, 6, 8, 12, 16, 24, 32, 48>{});
 }
@@ -1783,6 +1791,8 @@ WindowForm<S> window_form(const typename S::Consts& c, int64_t L)
         f.exact = moderate && pow2(c.c2, 0, 8) && pow2(c.c1, -8, 8);
         f.fused = fma ? f.exact : moderate;
         f.ops = fma ? (f.exact ? 18 : 22) : (f.exact ? 21 : (f.fused ? 27 : 30));
+    } else if constexpr (has_faces<S>::value) {
+        f.ops = 480;
     } else if constexpr (std::is_base_of_v<HeatFma<typename S::T>, S>) {
         f.ops = 3;
     } else if constexpr (has_fused_form<S>) {
@@ -1855,7 +1865,7 @@ int run_window(void* uv, int64_t nx, int64_t nsteps, int id, const typename S::C
         if constexpr (is_ks<S>) {
             a.big = 1e30;
             a.tiny = form.exact ? std::ldexp(1.0, -400) : 0.0;
-        } else {
+        } else if constexpr (!has_faces<S>::value) {
             a.big = std::numeric_limits<T>::max() / (s == 0 ? 16 : 8);
             a.tiny = form.e > 0 ? std::ldexp(T(1), std::numeric_limits<T>::min_exponent - 1 +
                                                        form.e * a.steps)
@@ -1888,6 +1898,7 @@ int window_dispatch(void* u, int64_t nx, int64_t nsteps, int32_t id, const doubl
     case SWEPT_HEAT_F32: return run_window<HeatF32>(u, nx, nsteps, id, heat32_consts(params));
     case SWEPT_HEAT_F64_FMA: return run_window<HeatFmaF64>(u, nx, nsteps, id, heat64_consts(params));
     case SWEPT_KS_F64: return run_window<KSF64>(u, nx, nsteps, id, ks_consts(params));
+    case SWEPT_EULER_F64: return run_window<EulerF64>(u, nx, nsteps, id, euler_consts(params));
     case SWEPT_KS_F64_FMA: return run_window<KSFmaF64>(u, nx, nsteps, id, ks_consts(params));
     default: return run_window<HeatFmaF32>(u, nx, nsteps, id, heat32_consts(params));
     }
@@ -1911,8 +1922,7 @@ size_t plan_scratch(const Plan& p, int64_t nx, int id)
 // schedule to be faster for the stencil and size class.
 bool use_window(int id, int64_t nx)
 {
-    if (!kWindows || !window_id(id) || g_ctx.mode != SWEPT_MODE_AUTO || g_ctx.tile_w != 0 ||
-        g_ctx.ppl != 0)
+    if (!kWindows || g_ctx.mode != SWEPT_MODE_AUTO || g_ctx.tile_w != 0 || g_ctx.ppl != 0)
         return false;
     const auto it = g_tuned.find(tune_key(id, nx));
     return it == g_tuned.end() || it->second.window;
@@ -2330,7 +2340,7 @@ int autotune(int64_t nx, int64_t nsteps, int id, const double* params, double* r
             }
         }
     }
-    if (kWindows && window_id(id)) {   // the window schedule, over at most 1024 steps
+    if (kWindows) {   // the window schedule, over at most 1024 steps
         const int64_t np = std::min<int64_t>(nsteps, 1024);
         rc = time_best([&] { return window_dispatch(f.p, nx, np, id, params); }, 3, &t);
         if (rc)

@@ -141,6 +141,17 @@ def test_ks_leaves_the_fused_range(sw, oracle_mod, par, fma):
     assert not np.all(np.isfinite(oracle(growing, 40, *par)))   # the case does leave the range
 
 
+@pytest.mark.parametrize("smooth", [False, True])
+@pytest.mark.parametrize("n,nsteps", [
+    (3, 1), (3, 2), (7, 9), (63, 3), (64, 1), (129, 25), (1000, 60), (4097, 33),
+    (65536 + 16, 21), (1 << 18, 7),
+])
+def test_euler_bitwise(sw, oracle_mod, n, nsteps, smooth):
+    q0 = workloads.euler_smooth(n, seed=n) if smooth else workloads.euler_mirrored_sod(n)
+    par = [workloads.EULER_CFL / n, 1.0 / n, workloads.EULER_GAMMA]
+    assert same_bits(run(sw, q0, nsteps, "euler", par), oracle_mod.euler(q0, nsteps, *par))
+
+
 @pytest.mark.parametrize("n,W", [(4096, 128), (65536, 1024)])
 def test_profiled_stages_are_reported(sw, n, W):
     import torch
