@@ -291,6 +291,15 @@ int swept_naive_substep_advance(void *u, int64_t nx, int64_t nsteps, int32_t ste
  * stencil_id[j] with parameters params[2j], params[2j+1] (heat reads the
  * first).  Every instance gets exactly the bits its own swept_advance would.
  *
+ * With every setting at its default (SWEPT_MODE_AUTO, no tile width or pairs
+ * per lane, swept_set_batch_schedule's defaults) the batch runs on register
+ * windows: per stage one launch per stencil over the tiles of the instances
+ * that still have steps to go, each instance on windows of its own ring (any
+ * length, no cover), between its field and a spare copy in the scratch.  The
+ * tables of a call pass through pinned host memory without a wait for the work
+ * enqueued before; the call cannot be captured into a graph (SWEPT_EHIP).  Other
+ * settings run the swept schedules described next.
+ *
  * Each instance of 2h points (h = nx/2 for even nx) is tiled by T = ceil(h/k)
  * tiles: T-1 of width 2k and one of the remainder 2(h - (T-1)k) (k =
  * tile_w/2 of swept_set_tuning if set, else the depth swept_autotune_batch
@@ -410,7 +419,8 @@ int swept_autotune(int64_t nx, int64_t nsteps, int32_t stencil_id, const double 
  * runs 6144 sub-timesteps, the others in proportion) under the current
  * schedule, best of two runs each, choosing the depth k in {128, 256, 384,
  * 512} for KS and then for heat (each with the other's depth set, since the
- * two stencils' launches overlap), and keeps the choice for later batches.  depth_out (host, 3 entries indexed by stencil id)
+ * two stencils' launches overlap), and keeps the choice for later batches, or
+ * the register windows where they run the same probe faster.  depth_out (host, 3 entries indexed by stencil id)
  * receives the chosen depth, 0 for a stencil not in the batch.  Allocates
  * and frees its own probe fields; synchronizes the stream.
  */

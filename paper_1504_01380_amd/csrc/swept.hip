@@ -1905,6 +1905,326 @@ int window_dispatch(void* u, int64_t nx, int64_t nsteps, int32_t id, const doubl
 }
 #endif
 
+// The batch on register windows: per stage one launch per stencil over the
+// tiles of the instances with stages to go.  All instances of a stencil share
+// the window size and the deepest stage; each spreads its own steps over an
+// even number of stages.
+struct WindowBatchPlan {
+    int M = 0;
+    int64_t h = 0;
+    double cost = 1e300;
+};
+
+// points per lane the batch kernels are built for
+constexpr int kWindowBatchHeat[] = {4, 8, 16, 32};
+constexpr int kWindowBatchKs[] = {4, 8, 12, 18};
+
+// Least predicted time over the sizes and depths, from sums over the instances:
+// T = n/room + 1/2 tiles run (nsteps + h) rows each on 1024 SIMDs, or, where
+// that is longer, the most stages of one instance run one after another.
+[[maybe_unused]] WindowBatchPlan window_batch_plan(int id, int ops, int64_t hmax, double sn, double ss, double sns,
+                                  double count, int64_t smax)
+{
+    const int R = substeps_of(id);
+    const WindowCost c = window_cost(id, ops);
+    const bool ks = id == SWEPT_KS_F64;
+    WindowBatchPlan best;
+    for (int M : ks ? kWindowBatchKs : kWindowBatchHeat) {
+        const int64_t W = 64 * M;
+        for (int f = 1; f <= 14; ++f) {
+            const int64_t h = std::min({W * f / (32 * R), hmax, (smax + 1) / 2});
+            if (h < 1)
+                continue;
+            const double room = (double)(W - 2 * R * h);
+            const double stages = std::ceil((double)smax / (double)h);
+            const double rows = (sns + (double)h * sn) / room + 0.5 * (ss + count * (double)h);
+            const double full = rows * (5.0 + c.per * M) / 1024.0 +
+                                stages * 0.5 * (double)h * c.per * M;
+            const double alone = stages * (double)h * (c.lat + c.per * M);
+            const double mem = 16.0 * (sns / (double)h + sn) / 5000.0;
+            const double cost = stages * 2000.0 + std::max(full, alone) + 0.5 * mem;
+            if (cost < best.cost) {
+                best.M = M;
+                best.h = h;
+                best.cost = cost;
+            }
+        }
+    }
+    return best;
+}
+
+// Host tables of a batch on their way to the device: two pinned buffers used in
+// turn, each free again once the copy out of it has run (its event), so that
+// a call neither waits for the work enqueued before it nor overwrites a table
+// that has still to be copied.
+struct Staging {
+    unsigned char* host[2] = {nullptr, nullptr};
+    size_t bytes[2] = {0, 0};
+    hipEvent_t done[2] = {nullptr, nullptr};
+    int next = 0;
+};
+Staging g_staging;
+
+[[maybe_unused]] int staging_get(size_t bytes, unsigned char** out)
+{
+    Staging& g = g_staging;
+    const int i = g.next;
+    if (!g.done[i])
+        HIP_TRY(hipEventCreateWithFlags(&g.done[i], hipEventDisableTiming));
+    HIP_TRY(hipEventSynchronize(g.done[i]));
+    if (bytes > g.bytes[i]) {
+        if (g.host[i]) {
+            HIP_TRY(hipHostFree(g.host[i]));
+            g.host[i] = nullptr;
+            g.bytes[i] = 0;
+        }
+        void* p = nullptr;
+        const size_t want = bytes + bytes / 4;
+        const hipError_t e = hipHostMalloc(&p, want, hipHostMallocDefault);
+        if (e != hipSuccess) {
+            (void)hipGetLastError();
+            return fail(SWEPT_ENOMEM, "hipHostMalloc of %zu bytes for the batch tables failed: %s",
+                        want, hipGetErrorString(e));
+        }
+        g.host[i] = static_cast<unsigned char*>(p);
+        g.bytes[i] = want;
+    }
+    *out = g.host[i];
+    return SWEPT_OK;
+}
+
+// copy the tables to the device on the library's stream
+[[maybe_unused]] int staging_put(void* dst, size_t bytes)
+{
+    Staging& g = g_staging;
+    const int i = g.next;
+    HIP_TRY(hipMemcpyAsync(dst, g.host[i], bytes, hipMemcpyHostToDevice, g_ctx.stream));
+    HIP_TRY(hipEventRecord(g.done[i], g_ctx.stream));
+    g.next = 1 - i;
+    return SWEPT_OK;
+}
+
+void staging_release()
+{
+    for (int i = 0; i < 2; ++i) {
+        if (g_staging.host[i])
+            (void)hipHostFree(g_staging.host[i]);
+        if (g_staging.done[i])
+            (void)hipEventDestroy(g_staging.done[i]);
+    }
+    g_staging = Staging{};
+}
+
+// Whether a batch runs on windows: the automatic setting (no tile width, pairs
+// per lane, mode or batch schedule chosen), unless swept_autotune_batch found
+// the tuned swept schedule faster.
+bool g_batch_windows = true;   // swept_autotune_batch's verdict
+
+bool use_window_batch()
+{
+    return kWindows && g_batch_windows && g_ctx.mode == SWEPT_MODE_AUTO && g_ctx.tile_w == 0 &&
+           g_ctx.ppl == 0 && g_batch_sched == SWEPT_BATCH_PERSISTENT && g_spin_limit == 0 &&
+           g_chunk == 0 && g_queues == 0;
+}
+
+#ifdef SWEPT_COUNT_UPDATES
+int run_window_batch(void* const*, const int64_t*, const int64_t*, const int32_t*, const double*,
+                     int64_t)
+{
+    return fail(SWEPT_EUNSUPPORTED, "the counting build has no window schedule");
+}
+#else
+// one stencil of a batch: its instances, tasks and launches
+template <class S>
+struct WindowBatch {
+    std::vector<WindowInst<S>> inst;
+    std::vector<int64_t> stages;       // per instance
+    std::vector<BatchTask> tasks;
+    std::vector<int64_t> live;         // live[s]: tasks of stage s
+    WindowBatchPlan plan;
+
+    // instances j of ids[j] == id, in the order given
+    void build(int id, const std::vector<int64_t>& js, void* const* u, const int64_t* nx,
+               const int64_t* nsteps, const std::vector<WindowForm<S>>& forms,
+               const std::vector<typename S::Consts>& consts)
+    {
+        if (js.empty())
+            return;
+        double sn = 0, ss = 0, sns = 0;
+        int64_t smax = 0, hmax = int64_t(1) << 40;
+        int ops = 0;
+        for (size_t q = 0; q < js.size(); ++q) {
+            const int64_t j = js[q];
+            sn += (double)nx[j];
+            ss += (double)nsteps[j];
+            sns += (double)nx[j] * (double)nsteps[j];
+            smax = std::max(smax, nsteps[j]);
+            ops = std::max(ops, forms[q].ops);
+            hmax = std::min(hmax, forms[q].hmax);
+        }
+        plan = window_batch_plan(id, ops, hmax, sn, ss, sns, (double)js.size(), smax);
+        const int64_t room = 64 * plan.M - 2 * S::NPHASE * plan.h;
+        inst.resize(js.size());
+        stages.resize(js.size());
+        std::vector<int64_t> tiles(js.size());
+        std::vector<int> order(js.size());
+        for (size_t q = 0; q < js.size(); ++q) {
+            const int64_t j = js[q];
+            WindowInst<S>& I = inst[q];
+            int64_t st = (nsteps[j] + plan.h - 1) / plan.h;
+            st += st & 1;
+            const int64_t t = (nx[j] + room - 1) / room;
+            I.u = static_cast<typename S::T*>(u[j]);
+            I.n = nx[j];
+            I.own = (int)std::min(room, ((nx[j] + t - 1) / t + 15) / 16 * 16);
+            I.base = (int)(nsteps[j] / st);
+            I.rem = (int)(nsteps[j] % st);
+            I.fused = forms[q].fused;
+            I.e = is_ks<S> ? (int)forms[q].exact : forms[q].e;
+            I.c = consts[q];
+            stages[q] = st;
+            tiles[q] = (nx[j] + I.own - 1) / I.own;
+            order[q] = (int)q;
+        }
+        std::stable_sort(order.begin(), order.end(),
+                         [&](int a, int b) { return stages[(size_t)a] > stages[(size_t)b]; });
+        live.assign((size_t)stages[(size_t)order[0]], 0);
+        for (int q : order) {
+            for (int64_t t = 0; t < tiles[(size_t)q]; ++t)
+                tasks.push_back(BatchTask{q, (int)t});
+            // a later instance has no more stages: the last write of each entry stands
+            live[(size_t)stages[(size_t)q] - 1] = (int64_t)tasks.size();
+        }
+        for (size_t s = live.size() - 1; s-- > 0;)
+            live[s] = std::max(live[s], live[s + 1]);
+    }
+
+    size_t table_bytes() const
+    {
+        return (inst.size() * sizeof(inst[0]) + 255) / 256 * 256 +
+               (tasks.size() * sizeof(BatchTask) + 255) / 256 * 256;
+    }
+
+    // lay the tables out at `host`, to be read at `dev`
+    void lay_out(unsigned char* host, unsigned char* dev)
+    {
+        const size_t at = (inst.size() * sizeof(inst[0]) + 255) / 256 * 256;
+        std::memcpy(host, inst.data(), inst.size() * sizeof(inst[0]));
+        std::memcpy(host + at, tasks.data(), tasks.size() * sizeof(BatchTask));
+        args.inst = reinterpret_cast<const WindowInst<S>*>(dev);
+        args.tasks = reinterpret_cast<const BatchTask*>(dev + at);
+    }
+
+    WindowBatchArgs<S> args{};
+
+    template <int... MS>
+    void launch(int64_t s, std::integer_sequence<int, MS...>)
+    {
+        args.stage = (int)s;
+        args.count = (unsigned)live[(size_t)s];
+        const dim3 grid((args.count + 7) / 8 * 8), block(64);
+        auto one = [&](auto m) {
+            constexpr int MM = decltype(m)::value;
+            if (plan.M == MM)
+                hipLaunchKernelGGL((window_batch_kernel<S, MM>), grid, block, 0, g_ctx.stream, args);
+        };
+        (one(std::integral_constant<int, MS>{}), ...);
+    }
+};
+
+int run_window_batch(void* const* u, const int64_t* nx, const int64_t* nsteps, const int32_t* ids,
+                     const double* params, int64_t count)
+{
+    // the tables pass through host memory that later calls reuse
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    HIP_TRY(hipStreamIsCapturing(g_ctx.stream, &cap));
+    if (cap != hipStreamCaptureStatusNone)
+        return fail(SWEPT_EHIP, "swept_advance_batch cannot be captured into a graph");
+    std::vector<int64_t> jh, jk;
+    std::vector<WindowForm<HeatF64>> fh;
+    std::vector<WindowForm<KSF64>> fk;
+    std::vector<HeatF64::Consts> ch;
+    std::vector<KSF64::Consts> ck;
+    bool any_heat = false, fusable = true;
+    for (int64_t j = 0; j < count; ++j) {
+        const int64_t L = nsteps[j] * substeps_of(ids[j]);
+        if (ids[j] == SWEPT_HEAT_F64) {
+            const HeatF64::Consts c = heat64_consts(params + 2 * j);
+            const WindowForm<HeatF64> f = window_form<HeatF64>(c, L);
+            any_heat = true;
+            fusable = fusable && f.fused;
+            if (L > 0) {
+                jh.push_back(j);
+                fh.push_back(f);
+                ch.push_back(c);
+            }
+        } else if (L > 0) {
+            const KSF64::Consts c = ks_consts(params + 2 * j);
+            jk.push_back(j);
+            fk.push_back(window_form<KSF64>(c, L));
+            ck.push_back(c);
+        }
+    }
+    // one decision on the fused heat forms for the whole batch
+    if (!fusable)
+        for (auto& f : fh)
+            f = WindowForm<HeatF64>{};
+    WindowBatch<HeatF64> h;
+    WindowBatch<KSF64> k;
+    h.build(SWEPT_HEAT_F64, jh, u, nx, nsteps, fh, ch);
+    k.build(SWEPT_KS_F64, jk, u, nx, nsteps, fk, ck);
+    if (h.tasks.size() >= (size_t(1) << 30) || k.tasks.size() >= (size_t(1) << 30))
+        return fail(SWEPT_EUNSUPPORTED, "swept_advance_batch: too many tiles");
+
+    // scratch: the tables, then the spare fields
+    const size_t bh = h.table_bytes(), bk = k.table_bytes();
+    auto al = [](int64_t n) { return ((size_t)n * sizeof(double) + 255) / 256 * 256; };
+    size_t spare = 0;
+    for (int64_t j : jh)
+        spare += al(nx[j]);
+    for (int64_t j : jk)
+        spare += al(nx[j]);
+    if (bh + bk > 0) {
+        int rc = ensure_scratch(bh + bk + spare);
+        if (rc)
+            return rc;
+        unsigned char* dev = static_cast<unsigned char*>(g_ctx.scratch);
+        unsigned char* field = dev + bh + bk;
+        for (size_t q = 0; q < jh.size(); ++q) {
+            h.inst[q].spare = reinterpret_cast<double*>(field);
+            field += al(nx[jh[q]]);
+        }
+        for (size_t q = 0; q < jk.size(); ++q) {
+            k.inst[q].spare = reinterpret_cast<double*>(field);
+            field += al(nx[jk[q]]);
+        }
+        unsigned char* host = nullptr;
+        rc = staging_get(bh + bk, &host);
+        if (rc)
+            return rc;
+        h.lay_out(host, dev);
+        k.lay_out(host + bh, dev + bh);
+        rc = staging_put(dev, bh + bk);
+        if (rc)
+            return rc;
+    }
+    if (any_heat) {
+        g_ctx.last_batch = false;
+        g_ctx.last_form = fusable ? SWEPT_FORM_FUSED : SWEPT_FORM_CANONICAL;
+        g_ctx.last_guard = fusable ? ++g_call_id : 0;
+        h.args.guard = g_ctx.last_guard;
+    }
+    for (size_t s = 0; s < std::max(h.live.size(), k.live.size()); ++s) {
+        if (s < k.live.size())
+            k.launch((int64_t)s, std::integer_sequence<int, 4, 8, 12, 18>{});
+        if (s < h.live.size())
+            h.launch((int64_t)s, std::integer_sequence<int, 4, 8, 16, 32>{});
+    }
+    HIP_TRY(hipGetLastError());
+    return SWEPT_OK;
+}
+#endif
+
 // The scratch the swept or naive schedule of a plan takes (run_swept,
 // run_ragged, run_naive_*): what bounds swept_advance_noalloc's requests.
 size_t plan_scratch(const Plan& p, int64_t nx, int id)
@@ -2413,6 +2733,7 @@ int autotune_batch(const int64_t* nx, const int64_t* nsteps, const int32_t* ids,
     // KS first (most of the work), then heat.  Depths are multiples of the
     // band size 128 (two pairs per lane), so that the square regions can take
     // the continuous-band schedule.
+    double swept_t = 1e30;
     for (int id : {SWEPT_HEAT_F64, SWEPT_KS_F64})
         g_batch_want[id] = kBatchWantDefault;
     for (int id : {SWEPT_KS_F64, SWEPT_HEAT_F64}) {
@@ -2436,8 +2757,17 @@ int autotune_batch(const int64_t* nx, const int64_t* nsteps, const int32_t* ids,
         }
         g_batch_want[id] = best;
         want_out[id] = best;
+        swept_t = best_t;
         if (rc)
             break;
+    }
+    if (!rc && kWindows) {   // the window schedule on the same probe
+        double t;
+        rc = time_best([&] {
+            return run_window_batch(up.data(), nxs.data(), ns.data(), is.data(), ps.data(),
+                                    (int64_t)sel.size());
+        }, 2, &t);
+        g_batch_windows = !rc && t < swept_t;
     }
     HIP_TRY(hipStreamSynchronize(g_ctx.stream));
     batch_release();  // its graph points at the probe fields
@@ -2650,7 +2980,8 @@ int swept_advance_batch(void* const* u, const int64_t* nx, const int64_t* nsteps
     }
     if (count == 0)
         return SWEPT_OK;
-    int rc = run_batch(u, nx, nsteps, stencil_id, params, count);
+    int rc = use_window_batch() ? run_window_batch(u, nx, nsteps, stencil_id, params, count)
+                                : run_batch(u, nx, nsteps, stencil_id, params, count);
     if (rc)
         return rc;
     HIP_TRY(hipGetLastError());
@@ -2725,6 +3056,7 @@ int swept_clear_tuning(void)
     g_tuned.clear();
     for (int64_t& w : g_batch_want)
         w = 0;
+    g_batch_windows = true;
     return SWEPT_OK;
 }
 
@@ -2932,6 +3264,7 @@ void swept_finalize(void)
         (void)hipFree(g_ctx.fault);
     release_events();
     batch_release();
+    staging_release();
     swept_clear_tuning();
     g_batch_sched = SWEPT_BATCH_PERSISTENT;
     g_spin_limit = 0;

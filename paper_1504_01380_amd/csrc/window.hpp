@@ -27,6 +27,8 @@
 // step (one wave per SIMD and no two-rows-per-level diamond).
 #pragma once
 
+#include <limits>
+
 #include "kernels.hpp"
 
 namespace swept {
@@ -370,18 +372,11 @@ __device__ __forceinline__ void ks_advance(double (&u)[M], const WindowArgs<S>& 
     ks_rows<S, kKsWritten, M>(u, g.steps, g.c);
 }
 
-// One stage: workgroup = one wave = one tile.  Consecutive tiles go to the
-// same XCD (workgroups are dealt to the eight XCDs in turn), so that the
-// halos neighbouring tiles share are read through one L2.
+// The windows of tile `tile`: load, advance, store the owned points.
 template <class S, int M>
-__global__ __launch_bounds__(64) void window_kernel(WindowArgs<S> g)
+__device__ __forceinline__ void window_tile(const WindowArgs<S>& g, unsigned tile)
 {
     using T = typename S::T;
-    const int lane = threadIdx.x;
-    const unsigned per = (unsigned)(g.tiles + 7) / 8;
-    const unsigned tile = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
-    if (tile >= (unsigned)g.tiles)
-        return;
     const int64_t t0 = (int64_t)tile * g.own;
     const int64_t x0 = t0 - g.halo;
     T u[M];
@@ -394,7 +389,7 @@ __global__ __launch_bounds__(64) void window_kernel(WindowArgs<S> g)
         window_advance<S, M>(u, g);
     const int64_t left = g.n - t0;
     const int cnt = (int)(left < g.own ? left : g.own);
-    const int c0 = lane * M - g.halo;   // this lane's first column among the owned points
+    const int c0 = (int)threadIdx.x * M - g.halo;   // this lane's first column among the owned
     T* o = g.out + (t0 + c0);
     if (c0 >= 0 && c0 + M <= cnt) {
 #pragma unroll
@@ -406,6 +401,85 @@ __global__ __launch_bounds__(64) void window_kernel(WindowArgs<S> g)
             if (c0 + q >= 0 && c0 + q < cnt)
                 o[q] = u[q];
     }
+}
+
+// Workgroups are dealt to the eight XCDs in turn: workgroup b of a launch of
+// `count` takes an index such that each XCD has a contiguous run of them
+// (count or more: none).
+__device__ __forceinline__ unsigned xcd_run(unsigned b, unsigned count)
+{
+    const unsigned per = (count + 7) / 8, x = b & 7, i = b >> 3;
+    return i < per ? x * per + i : count;
+}
+
+// One stage of one field: workgroup = one wave = one tile.  Neighbouring tiles
+// run on one XCD, so that the halos they share are read through one L2.
+template <class S, int M>
+__global__ __launch_bounds__(64) void window_kernel(WindowArgs<S> g)
+{
+    const unsigned tile = xcd_run(blockIdx.x, (unsigned)g.tiles);
+    if (tile < (unsigned)g.tiles)
+        window_tile<S, M>(g, tile);
+}
+
+// ------------------------------------------------------------------ batch
+// One stage of every instance of one stencil that still has stages to go: the
+// tasks (instance, tile) are sorted by their instance's stage count, so those
+// of stage s are the first `count`.  Each instance has its own even number of
+// stages, at most h steps each, and its own owned width (equal tiles); odd
+// lengths need no cover.  Stages alternate between the instance's field and
+// its spare copy.
+template <class S>
+struct WindowInst {
+    typename S::T* u;
+    typename S::T* spare;
+    int64_t n;
+    int own;
+    int base, rem;     // stage s advances base + (s < rem) steps
+    int fused;         // as WindowArgs::fused
+    int e;             // heat: r = 2^-e (0: no exact-product form); KS: 1 for the exact-product form
+    typename S::Consts c;
+};
+
+template <class S>
+struct WindowBatchArgs {
+    const WindowInst<S>* inst;
+    const BatchTask* tasks;
+    unsigned count;
+    int stage;
+    unsigned long long guard;
+};
+
+template <class S, int M>
+__global__ __launch_bounds__(64) void window_batch_kernel(WindowBatchArgs<S> b)
+{
+    using T = typename S::T;
+    const unsigned i = xcd_run(blockIdx.x, b.count);
+    if (i >= b.count)
+        return;
+    const BatchTask task = b.tasks[i];
+    const WindowInst<S>& I = b.inst[task.inst];
+    const bool odd = (b.stage & 1) != 0;
+    WindowArgs<S> g;
+    g.in = odd ? I.spare : I.u;
+    g.out = odd ? I.u : I.spare;
+    g.n = I.n;
+    g.own = I.own;
+    g.steps = I.base + (b.stage < I.rem);
+    g.halo = g.steps * S::NPHASE;
+    g.c = I.c;
+    g.fused = I.fused;
+    if constexpr (is_ks<S>) {
+        g.big = 1e30;
+        g.tiny = I.e != 0 ? __hiloint2double(0x26f00000, 0) : 0.0;   // 2^-400
+        g.guard = 0;
+    } else {
+        static_assert(sizeof(T) == 8, "the batch takes binary64 stencils");
+        g.big = std::numeric_limits<T>::max() / (b.stage == 0 ? 16 : 8);
+        g.tiny = I.e != 0 ? __hiloint2double((1 + I.e * g.steps) << 20, 0) : 0.0;   // 2^(e*steps - 1022)
+        g.guard = b.stage == 0 ? b.guard : 0;
+    }
+    window_tile<S, M>(g, (unsigned)task.tile);
 }
 
 }  // namespace swept

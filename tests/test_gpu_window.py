@@ -152,6 +152,41 @@ def test_euler_bitwise(sw, oracle_mod, n, nsteps, smooth):
     assert same_bits(run(sw, q0, nsteps, "euler", par), oracle_mod.euler(q0, nsteps, *par))
 
 
+@pytest.mark.parametrize("spread", [False, True])
+def test_batch_bitwise(sw, oracle_mod, spread):
+    """Batches on windows: rings far smaller than a window and larger ones,
+    odd and even, runs of no, one, a few and many steps (so instances leave the
+    stages at different times), every form of either stencil."""
+    import torch
+    sizes = [3, 4, 5, 63, 64, 65, 255, 1000, 4097] + ([20000, 65537] if spread else [])
+    insts = []
+    for q, n in enumerate(sizes):
+        for steps in (0, 1, 2, 3, 17, 150) + ((700,) if spread else ()):
+            st = "heat" if (q + steps) % 2 else "ks"
+            par = [[0.25, 0.3, 0.5][q % 3]] if st == "heat" else [KS_P, [0.004, 0.7]][q % 2]
+            u0 = workloads.white_noise(n, seed=n + steps)
+            insts.append((st, n, steps, par, u0 if st == "heat" else 0.2 * u0))
+    us = [torch.from_numpy(i[4].copy()).cuda() for i in insts]
+    for rep in range(3):      # the tables' host buffers are used in turn
+        for u, i in zip(us, insts):
+            u.copy_(torch.from_numpy(i[4]))
+        sw.advance_batch(us, [i[2] for i in insts], [i[0] for i in insts], [i[3] for i in insts])
+    torch.cuda.synchronize()
+    sw.sync()
+    assert sw.last_heat_form() == sw.FORM_FUSED
+    for (st, n, steps, par, u0), u in zip(insts, us):
+        want = oracle_mod.heat(u0, steps, *par) if st == "heat" else oracle_mod.ks(u0, steps, *par)
+        assert same_bits(u.cpu().numpy(), want), (st, n, steps, par)
+
+
+def test_batch_of_nothing(sw):
+    import torch
+    us = [torch.ones(10, dtype=torch.float64, device="cuda") for _ in range(3)]
+    sw.advance_batch(us, [0, 0, 0], ["heat", "ks", "heat"], [[0.25], KS_P, [0.3]])
+    torch.cuda.synchronize()
+    assert all(bool((u == 1).all()) for u in us)
+
+
 @pytest.mark.parametrize("n,W", [(4096, 128), (65536, 1024)])
 def test_profiled_stages_are_reported(sw, n, W):
     import torch
