@@ -461,6 +461,14 @@ int swept_stage_times(double *ms_out, int32_t *kind_out, int64_t cap, int64_t *c
  * sub-timestep's transposed Jacobian, applied in reverse order), evaluated
  * in a fixed order.
  *
+ * Automatic calls (SWEPT_MODE_AUTO, tile width and pairs per lane left at 0)
+ * run on register windows: a forward pass keeps the fields the reverse sweep
+ * reads (KS: every step's; heat: the window's, since its transposed step reads
+ * none) and the reverse sweep takes the cotangent back many steps per launch.
+ * Scratch: 8 * nx bytes for every field kept.  Calls for which that is over
+ * 4 GiB and over 1.5 times the swept adjoint's scratch, or cannot be had, and
+ * other tunings run the swept adjoint:
+ *
  * A forward swept pass keeps the V edges of every stage (one checkpoint per
  * sweep, 2*nx points per stage; u0 is only read); the stages then run in
  * reverse, each region recomputing its forward values from its checkpoint
@@ -503,7 +511,10 @@ int swept_naive_adjoint(const void *u0, void *grad_u0, int64_t nx, int64_t nstep
  * (two-sum) addition, so J does not depend on timing and its relative
  * rounding error is a few units of 1e-16 rather than growing with the number
  * of steps -- what a finite-difference check of the gradient differences.
- * Uses its own device buffer (nx doubles and 8 KiB), grown on demand.
+ * (Automatic calls keep the window's fields, 64 MiB of them at a time, and sum
+ * them in the same order, which gives the same J in fewer launches.)
+ * Uses its own device buffer (nx doubles, 8 KiB and those fields), grown on
+ * demand.
  */
 int swept_window_objective(const void *u0, int64_t nx, int64_t nsteps, int32_t stencil_id,
                            const double *params, int32_t nparams, int64_t window_first,

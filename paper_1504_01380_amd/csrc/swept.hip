@@ -1677,6 +1677,34 @@ size_t field_bytes(int id);
 constexpr int kWindowHeat[] = {2, 3, 4, 6, 8, 12, 16, 24, 32, 48};
 constexpr int kWindowKs[] = {2, 3, 4, 6, 8, 10, 12, 14, 16, 18, 20, 24};
 constexpr int kWindowEuler[] = {1, 2, 3, 4, 6};
+constexpr int kWindowAdj[] = {2, 3, 4, 6, 8};    // the adjoint, and stages that keep every step
+
+// What a plan is made for: the sizes built, points a step's dependence grows by
+// on either side (and once per stage beside that), bytes of one field value,
+// and the time of a row.
+struct WindowShape {
+    const int* sizes;
+    int count;
+    int radius, extra;
+    double bytes;
+    WindowCost cost;
+};
+
+template <size_t N>
+WindowShape window_shape(const int (&sizes)[N], int id, int ops)
+{
+    return WindowShape{sizes, (int)N, substeps_of(id), 0, (double)field_bytes(id),
+                       window_cost(id, ops)};
+}
+
+[[maybe_unused]] WindowShape window_shape(int id, int ops)
+{
+    switch (base_id(id)) {
+    case SWEPT_KS_F64: return window_shape(kWindowKs, id, ops);
+    case SWEPT_EULER_F64: return window_shape(kWindowEuler, id, ops);
+    default: return window_shape(kWindowHeat, id, ops);
+    }
+}
 
 // The window size and stage depth of least predicted time.  A stage costs a
 // launch and its loads and stores (about 2 us, and the field's bytes in and
@@ -1684,22 +1712,14 @@ constexpr int kWindowEuler[] = {1, 2, 3, 4, 6};
 // a row takes the longer of a lone wave's latency and the issue time of all
 // the waves of a SIMD.  Deep stages spread the launch, wide windows the halo;
 // few tiles (small grids) want small windows, whose rows are short.
-[[maybe_unused]] WindowPlan window_plan(int id, int64_t n, int64_t nsteps, int ops, int64_t hmax)
+[[maybe_unused]] WindowPlan window_plan(const WindowShape& shape, int64_t n, int64_t nsteps,
+                                        int64_t hmax)
 {
-    const int R = substeps_of(id);
-    const WindowCost c = window_cost(id, ops);
+    const int R = shape.radius;
+    const WindowCost c = shape.cost;
     WindowPlan best;
-    const int* sizes = kWindowHeat;
-    int nsizes = (int)std::size(kWindowHeat);
-    if (base_id(id) == SWEPT_KS_F64) {
-        sizes = kWindowKs;
-        nsizes = (int)std::size(kWindowKs);
-    } else if (id == SWEPT_EULER_F64) {
-        sizes = kWindowEuler;
-        nsizes = (int)std::size(kWindowEuler);
-    }
-    for (int i = 0; i < nsizes; ++i) {
-        const int M = sizes[i];
+    for (int i = 0; i < shape.count; ++i) {
+        const int M = shape.sizes[i];
         const int64_t W = 64 * M;
         int64_t last = 0;
         for (int f = 1; f <= 14; ++f) {
@@ -1711,7 +1731,7 @@ constexpr int kWindowEuler[] = {1, 2, 3, 4, 6};
             p.stages = (nsteps + h - 1) / h;
             p.stages += p.stages & 1;
             p.h = (nsteps + p.stages - 1) / p.stages;
-            const int64_t room = W - 2 * R * p.h;
+            const int64_t room = W - 2 * (R * p.h + shape.extra);
             p.M = M;
             p.tiles = (n + room - 1) / room;
             if (p.tiles > (int64_t(1) << 30))
@@ -1723,8 +1743,7 @@ constexpr int kWindowEuler[] = {1, 2, 3, 4, 6};
             const double w = (double)p.tiles / 1024.0;
             const double waves = w <= 8.0 ? std::ceil(w) : w + 0.5;
             const double row = std::max(c.lat + c.per * M, waves * (5.0 + c.per * M));
-            const double mem = (double)n * (double)field_bytes(id) *
-                               (1.0 + (double)W / (double)p.own) / 9000.0;
+            const double mem = (double)n * shape.bytes * (1.0 + (double)W / (double)p.own) / 9000.0;
             p.cost = (double)p.stages * (2000.0 + mem + (double)p.h * row);
             if (p.cost < best.cost)
                 best = p;
@@ -1733,14 +1752,20 @@ constexpr int kWindowEuler[] = {1, 2, 3, 4, 6};
     return best;
 }
 
-template <class S, int... MS>
+// time steps done before stage s of a plan: the run spread evenly over its stages
+[[maybe_unused]] int64_t stage_start(int64_t nsteps, int64_t stages, int64_t s)
+{
+    return nsteps / stages * s + nsteps % stages * s / stages;
+}
+
+template <class S, bool ALL = false, int... MS>
 void launch_window_of(const WindowArgs<S>& a, int M, hipStream_t st, std::integer_sequence<int, MS...>)
 {
     const dim3 grid((unsigned)((a.tiles + 7) / 8 * 8)), block(64);
     auto one = [&](auto m) {
         constexpr int MM = decltype(m)::value;
         if (M == MM)
-            hipLaunchKernelGGL((window_kernel<S, MM>), grid, block, 0, st, a);
+            hipLaunchKernelGGL((window_kernel<S, MM, ALL>), grid, block, 0, st, a);
     };
     (one(std::integral_constant<int, MS>{}), ...);
 }
@@ -1830,49 +1855,54 @@ unsigned long long window_record(const WindowForm<S>& f)
     }
 }
 
+// the arguments of a stage of `steps` steps, the first of its run or a later one
 template <class S>
-int run_window(void* uv, int64_t nx, int64_t nsteps, int id, const typename S::Consts& c)
+WindowArgs<S> window_args(const WindowPlan& p, const WindowForm<S>& form, int64_t nx,
+                          const typename S::Consts& c, int64_t steps, bool first)
 {
     using T = typename S::T;
-    const WindowForm<S> form = window_form<S>(c, nsteps * S::NPHASE);
-    const WindowPlan p = window_plan(id, nx, nsteps, form.ops, form.hmax);
-    if (p.M == 0)
-        return fail(SWEPT_EUNSUPPORTED, "nx = %lld is too long", (long long)nx);
-    int rc = ensure_scratch((size_t)nx * sizeof(T));
-    if (rc)
-        return rc;
-    T* buf[2] = {static_cast<T*>(uv), static_cast<T*>(scratch_base())};
-    const unsigned long long guard = window_record<S>(form);
-    if (g_ctx.profiling) {
-        rc = reserve_events(p.stages);
-        if (rc)
-            return rc;
-        HIP_TRY(hipEventRecord(g_ctx.events[0], g_ctx.stream));
-    }
     WindowArgs<S> a{};
     a.n = nx;
     a.own = p.own;
     a.tiles = (int)p.tiles;
+    a.steps = (int)steps;
+    a.halo = a.steps * S::NPHASE;
     a.c = c;
     a.fused = form.fused;
-    int64_t done = 0;
-    for (int64_t s = 0; s < p.stages; ++s) {
-        const int64_t next = nsteps / p.stages * (s + 1) + nsteps % p.stages * (s + 1) / p.stages;
-        a.in = buf[s & 1];
-        a.out = buf[(s + 1) & 1];
-        a.steps = (int)(next - done);
-        a.halo = a.steps * S::NPHASE;
-        if constexpr (is_ks<S>) {
-            a.big = 1e30;
-            a.tiny = form.exact ? std::ldexp(1.0, -400) : 0.0;
-        } else if constexpr (!has_faces<S>::value) {
-            a.big = std::numeric_limits<T>::max() / (s == 0 ? 16 : 8);
-            a.tiny = form.e > 0 ? std::ldexp(T(1), std::numeric_limits<T>::min_exponent - 1 +
-                                                       form.e * a.steps)
-                                : T(0);
-        }
+    if constexpr (is_ks<S>) {
+        a.big = 1e30;
+        a.tiny = form.exact ? std::ldexp(1.0, -400) : 0.0;
+    } else if constexpr (!has_faces<S>::value) {
+        a.big = std::numeric_limits<T>::max() / (first ? 16 : 8);
+        a.tiny = form.e > 0 ? std::ldexp(T(1), std::numeric_limits<T>::min_exponent - 1 +
+                                                   form.e * a.steps)
+                            : T(0);
+    }
+    return a;
+}
+
+// nsteps steps from `in` to `out` by way of `spare` (`in` may be `out`)
+template <class S>
+int window_stages(const typename S::T* in, typename S::T* out, typename S::T* spare, int64_t nx,
+                  int64_t nsteps, int id, const typename S::Consts& c, const WindowForm<S>& form,
+                  unsigned long long guard)
+{
+    const WindowPlan p = window_plan(window_shape(id, form.ops), nx, nsteps, form.hmax);
+    if (p.M == 0)
+        return fail(SWEPT_EUNSUPPORTED, "nx = %lld is too long", (long long)nx);
+    if (g_ctx.profiling) {
+        int rc = reserve_events(p.stages);
+        if (rc)
+            return rc;
+        HIP_TRY(hipEventRecord(g_ctx.events[0], g_ctx.stream));
+    }
+    for (int64_t s = 0; s < p.stages; ++s) {   // an even number of stages
+        const int64_t at = stage_start(nsteps, p.stages, s);
+        WindowArgs<S> a = window_args<S>(p, form, nx, c, stage_start(nsteps, p.stages, s + 1) - at,
+                                         s == 0);
+        a.in = s == 0 ? in : (s % 2 == 0 ? out : spare);
+        a.out = s % 2 == 0 ? spare : out;
         a.guard = s == 0 ? guard : 0;
-        done = next;
         launch_window<S>(a, p.M, g_ctx.stream);
         if (g_ctx.profiling) {
             g_ctx.kinds[(size_t)s] = 4;
@@ -1883,6 +1913,155 @@ int run_window(void* uv, int64_t nx, int64_t nsteps, int id, const typename S::C
     if (g_ctx.profiling)
         g_ctx.recorded = p.stages;
     return SWEPT_OK;
+}
+
+template <class S>
+int run_window(void* uv, int64_t nx, int64_t nsteps, int id, const typename S::Consts& c)
+{
+    using T = typename S::T;
+    int rc = ensure_scratch((size_t)nx * sizeof(T));
+    if (rc)
+        return rc;
+    const WindowForm<S> form = window_form<S>(c, nsteps * S::NPHASE);
+    T* u = static_cast<T*>(uv);
+    return window_stages<S>(u, u, static_cast<T*>(scratch_base()), nx, nsteps, id, c, form,
+                            window_record<S>(form));
+}
+
+// nsteps steps from `in`, every step's field kept: step j (from 1) at
+// kept + (j - 1)*nx
+template <class S>
+int window_keep(const typename S::T* in, typename S::T* kept, int64_t nx, int64_t nsteps, int id,
+                const typename S::Consts& c, const WindowForm<S>& form)
+{
+    if (nsteps <= 0)
+        return SWEPT_OK;
+    const WindowPlan p = window_plan(window_shape(kWindowAdj, id, form.ops), nx, nsteps, form.hmax);
+    if (p.M == 0)
+        return fail(SWEPT_EUNSUPPORTED, "nx = %lld is too long", (long long)nx);
+    for (int64_t s = 0; s < p.stages; ++s) {
+        const int64_t at = stage_start(nsteps, p.stages, s);
+        WindowArgs<S> a = window_args<S>(p, form, nx, c, stage_start(nsteps, p.stages, s + 1) - at,
+                                         false);
+        if (a.steps == 0)
+            continue;
+        a.in = at == 0 ? in : kept + (at - 1) * nx;
+        a.out = kept + at * nx;
+        launch_window_of<S, true>(a, p.M, g_ctx.stream, std::integer_sequence<int, 2, 3, 4, 6, 8>{});
+    }
+    HIP_TRY(hipGetLastError());
+    return SWEPT_OK;
+}
+
+// operations of a point in one transposed KS step (window_adjoint_kernel)
+constexpr int kAdjOps = 62;
+
+template <class S, int... MS>
+void launch_window_adjoint(const WindowAdjArgs<S>& a, int M, std::integer_sequence<int, MS...>)
+{
+    const dim3 grid((unsigned)((a.tiles + 7) / 8 * 8)), block(64);
+    auto one = [&](auto m) {
+        constexpr int MM = decltype(m)::value;
+        if (M == MM)
+            hipLaunchKernelGGL((window_adjoint_kernel<S, MM>), grid, block, 0, g_ctx.stream, a);
+    };
+    (one(std::integral_constant<int, MS>{}), ...);
+}
+
+// The adjoint on windows (window_adjoint_kernel).  The fields the reverse sweep
+// reads are kept from a forward pass: KS every step's, heat those of the
+// objective's window; heat's transposed step below the window (or without
+// one) reads no field and is the forward step itself, so that part of the
+// reverse sweep is a run of the cotangent.  Scratch: the kept fields and two
+// cotangents; SWEPT_ENOMEM, before anything is enqueued, if that cannot be had.
+template <class S>
+int run_window_adjoint(const typename S::T* u0, typename S::T* grad, int64_t nx, int64_t nsteps,
+                       int id, const typename S::Consts& c, int64_t win_first, double wgt,
+                       const typename S::T* cot)
+{
+    using T = typename S::T;
+    constexpr bool ks = is_ks<S>;
+    const int64_t from = std::max<int64_t>(win_first, 0);       // first step with a source
+    const bool windowed = from <= nsteps;
+    // steps whose fields are kept: kept0 .. nsteps
+    const int64_t kept0 = ks ? 1 : std::max<int64_t>(from, 1);
+    const int64_t nkept = ks || windowed ? nsteps - kept0 + 1 : 0;
+    const size_t field = ((size_t)nx * sizeof(T) + 255) / 256 * 256;
+    if ((double)nkept * (double)nx * sizeof(T) > 1e14)
+        return fail(SWEPT_ENOMEM, "the adjoint would keep %lld fields", (long long)nkept);
+    const size_t kept_b = ((size_t)nkept * (size_t)nx * sizeof(T) + 255) / 256 * 256;
+    int rc = ensure_scratch(2 * field + kept_b);
+    if (rc)
+        return rc;
+    unsigned char* base = static_cast<unsigned char*>(g_ctx.scratch);
+    T* lam[2] = {reinterpret_cast<T*>(base), reinterpret_cast<T*>(base + field)};
+    T* kept = reinterpret_cast<T*>(base + 2 * field);
+
+    // stage events belong to swept_advance
+    struct NoProfile {
+        bool on = g_ctx.profiling;
+        NoProfile() { g_ctx.profiling = false; }
+        ~NoProfile() { g_ctx.profiling = on; }
+    } no_profile;
+    const WindowForm<S> form = window_form<S>(c, nsteps * S::NPHASE);
+
+    // forward
+    if (nkept > 0) {
+        const T* at = u0;
+        int64_t done = 0;
+        if (kept0 > 1) {   // heat: up to the window
+            rc = window_stages<S>(u0, kept, lam[0], nx, kept0, id, c, form, 0);
+            if (rc)
+                return rc;
+            at = kept;
+            done = kept0;
+        }
+        rc = window_keep<S>(at, kept + (done > 0 ? nx : 0), nx, nsteps - done, id, c, form);
+        if (rc)
+            return rc;
+    }
+
+    // reverse, down to the first step whose field is read (at least the seed)
+    const int64_t stop = ks ? 0 : std::min(from, nsteps);
+    const int64_t total = nsteps - stop;
+    const T* in = cot;
+    int flip = 0;
+    if (windowed || ks || cot == nullptr) {
+        WindowShape shape = window_shape(kWindowAdj, id, ks ? kAdjOps : 6);
+        if (ks)
+            shape.extra = 2;
+        const WindowPlan p = window_plan(shape, nx, std::max<int64_t>(total, 1), int64_t(1) << 40);
+        if (p.M == 0)
+            return fail(SWEPT_EUNSUPPORTED, "nx = %lld is too long", (long long)nx);
+        WindowAdjArgs<S> a{};
+        a.u0 = u0;
+        a.kept = kept;
+        a.kept0 = kept0;
+        a.n = nx;
+        a.own = p.own;
+        a.tiles = (int)p.tiles;
+        a.win_first = win_first;
+        a.two_w = (T)(2.0 * wgt);
+        a.c = c;
+        int64_t done = 0;
+        for (int64_t s = 0; s < p.stages; ++s) {
+            const int64_t upto = stage_start(total, p.stages, s + 1);
+            if (upto == done && (total > 0 || s > 0))
+                continue;   // no steps, and not the seed alone
+            a.steps = (int)(upto - done);
+            a.halo = a.steps * S::NPHASE + shape.extra;
+            a.seed = done == 0;
+            a.first = nsteps - upto;
+            a.in = in;
+            a.out = a.first == 0 ? grad : lam[flip];
+            launch_window_adjoint<S>(a, p.M, std::integer_sequence<int, 2, 3, 4, 6, 8>{});
+            in = a.out;
+            flip ^= 1;
+            done = upto;
+        }
+        HIP_TRY(hipGetLastError());
+    }
+    return stop > 0 ? window_stages<S>(in, grad, lam[flip], nx, stop, id, c, form, 0) : SWEPT_OK;
 }
 
 #ifdef SWEPT_COUNT_UPDATES
@@ -2225,6 +2404,68 @@ int run_window_batch(void* const* u, const int64_t* nx, const int64_t* nsteps, c
 }
 #endif
 
+// The adjoint runs on windows in automatic calls on the grids the swept adjoint
+// takes, where the fields it keeps stay within 4 GiB or 1.5 times what the
+// swept adjoint would keep (it keeps 8 bytes a point for every step it needs,
+// the swept one 48 a point for every k/4 KS steps, 16 for every k heat steps).
+[[maybe_unused]] bool use_window_adjoint(int64_t nx, int64_t nsteps, int id, int64_t win_first)
+{
+    if (!kWindows || nsteps == 0 || g_ctx.mode != SWEPT_MODE_AUTO || g_ctx.tile_w != 0 ||
+        g_ctx.ppl != 0 || (id != SWEPT_HEAT_F64 && id != SWEPT_KS_F64))
+        return false;
+    const bool ks = id == SWEPT_KS_F64;
+    const int64_t k = ks ? adjoint_depth<KSF64>(nx, 0) : adjoint_depth<HeatF64>(nx, 0);
+    if (k == 0)
+        return false;
+    const int64_t keep = ks ? nsteps : std::max<int64_t>(0, nsteps - std::max<int64_t>(win_first, 1) + 1);
+    const double window = 8.0 * (double)nx * (double)keep;
+    const double swept = (ks ? 48.0 : 16.0) * (double)nx *
+                         (1.0 + (double)nsteps * substeps_of(id) / (double)k);
+    return window <= std::max(1.5 * swept, 4294967296.0);
+}
+
+#ifdef SWEPT_COUNT_UPDATES
+int window_keep_dispatch(const double*, double*, int64_t, int64_t, int, const double*)
+{
+    return fail(SWEPT_EUNSUPPORTED, "the counting build has no window schedule");
+}
+#else
+int window_keep_dispatch(const double* in, double* kept, int64_t nx, int64_t nsteps, int id,
+                         const double* params)
+{
+    auto run = [&](auto tag, const auto& c) {
+        using S = typename decltype(tag)::type;
+        return window_keep<S>(in, kept, nx, nsteps, id, c, window_form<S>(c, nsteps * S::NPHASE));
+    };
+    switch (id) {
+    case SWEPT_HEAT_F64: return run(stencil_tag<HeatF64>{}, heat64_consts(params));
+    case SWEPT_HEAT_F64_FMA: return run(stencil_tag<HeatFmaF64>{}, heat64_consts(params));
+    case SWEPT_KS_F64_FMA: return run(stencil_tag<KSFmaF64>{}, ks_consts(params));
+    default: return run(stencil_tag<KSF64>{}, ks_consts(params));
+    }
+}
+#endif
+
+#ifdef SWEPT_COUNT_UPDATES
+int window_adjoint_dispatch(const void*, void*, int64_t, int64_t, int32_t, const double*, int64_t,
+                            double, const void*)
+{
+    return SWEPT_ENOMEM;
+}
+#else
+int window_adjoint_dispatch(const void* u0, void* grad, int64_t nx, int64_t nsteps, int32_t id,
+                            const double* params, int64_t win_first, double wgt, const void* cot)
+{
+    const double* u = static_cast<const double*>(u0);
+    const double* c = static_cast<const double*>(cot);
+    double* g = static_cast<double*>(grad);
+    if (id == SWEPT_HEAT_F64)
+        return run_window_adjoint<HeatF64>(u, g, nx, nsteps, id, heat64_consts(params), win_first,
+                                           wgt, c);
+    return run_window_adjoint<KSF64>(u, g, nx, nsteps, id, ks_consts(params), win_first, wgt, c);
+}
+#endif
+
 // The scratch the swept or naive schedule of a plan takes (run_swept,
 // run_ragged, run_naive_*): what bounds swept_advance_noalloc's requests.
 size_t plan_scratch(const Plan& p, int64_t nx, int id)
@@ -2326,12 +2567,24 @@ int run_objective(const void* u0, int64_t nx, int64_t nsteps, int32_t id, const 
                   int64_t first, double wgt, const void* cot, double* J)
 {
     const size_t field = ((size_t)nx * sizeof(double) + 255) / 256 * 256;
-    int rc = ensure_obj(field + 4 * kObjBlocks * sizeof(double));
+    const int64_t wsteps = nsteps - std::max<int64_t>(first - 1, 0);   // steps inside the window
+    // fields of the window kept at once (64 MiB of them, at most 1024); fewer than
+    // four would not pay for the windows' halos
+    int64_t chunk = use_window(id, nx)
+                        ? std::min({wsteps, (int64_t(64) << 20) / (int64_t)field, int64_t(1024)})
+                        : 0;
+    if (chunk < 4)
+        chunk = 0;
+    const size_t part_b = (size_t)chunk * kObjBlocks * sizeof(double);
+    int rc = ensure_obj(field + 4 * kObjBlocks * sizeof(double) + part_b +
+                        (size_t)chunk * (size_t)nx * sizeof(double));
     if (rc)
         return rc;
     double* f = static_cast<double*>(g_ctx.obj);
     double* acc_sq = reinterpret_cast<double*>(static_cast<unsigned char*>(g_ctx.obj) + field);
     double* acc_dot = acc_sq + 2 * kObjBlocks;
+    double* part = acc_dot + 2 * kObjBlocks;
+    double* kept = part + (size_t)chunk * kObjBlocks;
     HIP_TRY(hipMemcpyAsync(f, u0, (size_t)nx * sizeof(double), hipMemcpyDeviceToDevice,
                            g_ctx.stream));
     hipLaunchKernelGGL(objective_clear_kernel, dim3(1), dim3(256), 0, g_ctx.stream, acc_sq,
@@ -2348,7 +2601,23 @@ int run_objective(const void* u0, int64_t nx, int64_t nsteps, int32_t id, const 
             sum_squares();
         const int64_t pre = std::max<int64_t>(first - 1, 0);
         rc = advance_dispatch(f, nx, pre, id, params);
-        for (int64_t j = pre + 1; j <= nsteps && rc == SWEPT_OK; ++j) {
+        int64_t j = pre + 1;
+        while (chunk > 0 && j <= nsteps && rc == SWEPT_OK) {
+            // the next steps' fields from one run of windows, and their sums
+            const int64_t m = std::min(chunk, nsteps - j + 1);
+            rc = window_keep_dispatch(f, kept, nx, m, id, params);
+            if (rc)
+                break;
+            hipLaunchKernelGGL(objective_partial_kernel, dim3(kObjBlocks, (unsigned)m),
+                               dim3(kObjThreads), 0, g_ctx.stream, kept, nx, part);
+            hipLaunchKernelGGL(objective_gather_kernel, dim3(1), dim3(kObjBlocks), 0, g_ctx.stream,
+                               part, (int)m, acc_sq);
+            j += m;
+            if (j <= nsteps || cot)
+                HIP_TRY(hipMemcpyAsync(f, kept + (m - 1) * nx, (size_t)nx * sizeof(double),
+                                       hipMemcpyDeviceToDevice, g_ctx.stream));
+        }
+        for (; j <= nsteps && rc == SWEPT_OK; ++j) {
             rc = naive_dispatch(f, nx, 1, id, params);
             if (rc == SWEPT_OK)
                 sum_squares();
@@ -3105,6 +3374,13 @@ int swept_adjoint(const void* u0, void* grad_u0, int64_t nx, int64_t nsteps, int
         return fail(SWEPT_EINVAL, "grad_u0 is NULL");
     if (!std::isfinite(window_weight))
         return fail(SWEPT_EINVAL, "window weight is not finite");
+    if (use_window_adjoint(nx, nsteps, stencil_id, window_first)) {
+        rc = window_adjoint_dispatch(u0, grad_u0, nx, nsteps, stencil_id, params, window_first,
+                                     window_weight, cot_final);
+        if (rc != SWEPT_ENOMEM)
+            return rc;
+        g_err.clear();   // the swept adjoint recomputes more and keeps less
+    }
     switch (stencil_id) {
     case SWEPT_HEAT_F64:
         return run_adjoint<HeatF64>(u0, grad_u0, nx, nsteps, params, heat64_consts(params),

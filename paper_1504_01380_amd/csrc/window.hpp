@@ -47,7 +47,7 @@ struct WindowArgs {
     int steps;       // time steps of this stage
     typename S::Consts c;
     // the evaluation forms this stage may take and their conditions on the
-    // values of a window (heat: window_advance; KS: ks_advance)
+    // values of a window (heat: heat_advance; KS: ks_advance)
     int fused;                  // 0: the operations as written only
     WindowBound<S> big;         // largest |u| of the fused forms
     WindowBound<S> tiny;        // smallest |u| of the exact-product form (0: not allowed)
@@ -84,9 +84,10 @@ __device__ __forceinline__ typename S::T heat_point(typename S::T u, typename S:
 // The sums of the next point are formed before a point is overwritten, so the
 // row updates in place and needs no register copies (a plain left-to-right
 // update cost one v_mov_b64 per point, 19% of the row).
-template <class S, int M>
+// each(j): called with the window at row j = 0, 1, ... done.
+template <class S, int M, class Each>
 __device__ __forceinline__ void heat_rows(typename S::T (&u)[M], int rows,
-                                          const typename S::Consts& k)
+                                          const typename S::Consts& k, Each&& each)
 {
     using T = typename S::T;
     for (int j = 0; j < rows; ++j) {
@@ -101,6 +102,7 @@ __device__ __forceinline__ void heat_rows(typename S::T (&u)[M], int rows,
             u[q] = heat_point<S>(u[q], s, k);
             s = sn;
         }
+        each(j);
     }
 }
 
@@ -112,8 +114,9 @@ __device__ __forceinline__ void heat_rows(typename S::T (&u)[M], int rows,
 // and MAX/8, which the run-length bound keeps out of reach, afterwards), and
 // for the exact-product form no nonzero |u| below `tiny`.  A wave decides for
 // itself; all forms give the same bits.
-template <class S, int M>
-__device__ __forceinline__ void window_advance(typename S::T (&u)[M], const WindowArgs<S>& g)
+template <class S, int M, class Each>
+__device__ __forceinline__ void heat_advance(typename S::T (&u)[M], const WindowArgs<S>& g,
+                                             Each&& each)
 {
     using T = typename S::T;
     if constexpr (has_fused_form<S>) {
@@ -127,16 +130,16 @@ __device__ __forceinline__ void window_advance(typename S::T (&u)[M], const Wind
             }
             if (!__any(bad)) {
                 if (!__any(sub))
-                    heat_rows<HeatExact<T>, M>(u, g.steps, g.c);
+                    heat_rows<HeatExact<T>, M>(u, g.steps, g.c, each);
                 else
-                    heat_rows<HeatLap<T>, M>(u, g.steps, g.c);
+                    heat_rows<HeatLap<T>, M>(u, g.steps, g.c, each);
                 return;
             }
             if (g.guard != 0 && threadIdx.x == 0)
                 atomicMax(&g_form_mark, g.guard);
         }
     }
-    heat_rows<S, M>(u, g.steps, g.c);
+    heat_rows<S, M>(u, g.steps, g.c, each);
 }
 
 // ------------------------------------------------------------------- KS
@@ -230,8 +233,9 @@ __device__ __forceinline__ void ks_half(const double (&a)[M], const double (&u)[
 
 // `steps` KS steps of the window; returns (kKsLap, kKsExact) whether every
 // step's u stayed in the form's range
-template <class S, int FORM, int M>
-__device__ __forceinline__ bool ks_rows(double (&u)[M], int steps, const KSF64::Consts& k)
+template <class S, int FORM, int M, class Each>
+__device__ __forceinline__ bool ks_rows(double (&u)[M], int steps, const KSF64::Consts& k,
+                                        Each&& each)
 {
     const double c1s = k.c1 / k.c2;   // exact where it is used (kKsExact)
     const double ch = FORM == kKsExact ? k.h * k.c2 : k.h;
@@ -241,6 +245,7 @@ __device__ __forceinline__ bool ks_rows(double (&u)[M], int steps, const KSF64::
     for (int s = 0; s < steps; ++s) {
         ks_half<S, FORM, M>(u, u, v, ch, k, c1s);
         ks_half<S, FORM, M>(v, u, u, cf, k, c1s);
+        each(s);
         if constexpr (FORM != kKsWritten) {
 #pragma unroll
             for (int q = 0; q < M; q += 2) {
@@ -345,8 +350,9 @@ __device__ __forceinline__ void window_load(T (&u)[M], const T* in, int64_t n, i
 
 // A KS stage of the window: the cheapest form its values allow, and the
 // operations as written where a value leaves the form's range on the way.
-template <class S, int M>
-__device__ __forceinline__ void ks_advance(double (&u)[M], const WindowArgs<S>& g, int64_t x0)
+template <class S, int M, class Each>
+__device__ __forceinline__ void ks_advance(double (&u)[M], const WindowArgs<S>& g, int64_t x0,
+                                           Each&& each)
 {
     if (g.fused != 0) {
         bool in = true, small = g.tiny == 0.0;
@@ -359,38 +365,25 @@ __device__ __forceinline__ void ks_advance(double (&u)[M], const WindowArgs<S>& 
         if (__all(in)) {
             bool ok;
             if (!__any(small))
-                ok = ks_rows<S, kKsExact, M>(u, g.steps, g.c);
+                ok = ks_rows<S, kKsExact, M>(u, g.steps, g.c, each);
             else if constexpr (!is_ks_fma<S>)
-                ok = ks_rows<S, kKsLap, M>(u, g.steps, g.c);
+                ok = ks_rows<S, kKsLap, M>(u, g.steps, g.c, each);
             else
-                ok = ks_rows<S, kKsWritten, M>(u, g.steps, g.c);
+                ok = ks_rows<S, kKsWritten, M>(u, g.steps, g.c, each);
             if (ok)
                 return;
             window_load<double, M>(u, g.in, g.n, x0);
         }
     }
-    ks_rows<S, kKsWritten, M>(u, g.steps, g.c);
+    ks_rows<S, kKsWritten, M>(u, g.steps, g.c, each);
 }
 
-// The windows of tile `tile`: load, advance, store the owned points.
-template <class S, int M>
-__device__ __forceinline__ void window_tile(const WindowArgs<S>& g, unsigned tile)
+// Store the owned points [t0, t0 + cnt) of a window whose column `halo` is t0.
+template <class T, int M>
+__device__ __forceinline__ void window_store(const T (&u)[M], T* out, int64_t t0, int halo, int cnt)
 {
-    using T = typename S::T;
-    const int64_t t0 = (int64_t)tile * g.own;
-    const int64_t x0 = t0 - g.halo;
-    T u[M];
-    window_load<T, M>(u, g.in, g.n, x0);
-    if constexpr (is_ks<S>)
-        ks_advance<S, M>(u, g, x0);
-    else if constexpr (has_faces<S>::value)
-        euler_advance<S, M>(u, g);
-    else
-        window_advance<S, M>(u, g);
-    const int64_t left = g.n - t0;
-    const int cnt = (int)(left < g.own ? left : g.own);
-    const int c0 = (int)threadIdx.x * M - g.halo;   // this lane's first column among the owned
-    T* o = g.out + (t0 + c0);
+    const int c0 = (int)threadIdx.x * M - halo;   // this lane's first column among the owned
+    T* o = out + (t0 + c0);
     if (c0 >= 0 && c0 + M <= cnt) {
 #pragma unroll
         for (int q = 0; q < M; ++q)
@@ -401,6 +394,34 @@ __device__ __forceinline__ void window_tile(const WindowArgs<S>& g, unsigned til
             if (c0 + q >= 0 && c0 + q < cnt)
                 o[q] = u[q];
     }
+}
+
+// One tile's stage: load, advance, store the owned points.  ALL: every step's
+// field is stored, step j of the stage (from 0) at out + j*n.
+template <class S, int M, bool ALL = false>
+__device__ __forceinline__ void window_tile(const WindowArgs<S>& g, unsigned tile)
+{
+    using T = typename S::T;
+    const int64_t t0 = (int64_t)tile * g.own;
+    const int64_t x0 = t0 - g.halo;
+    const int64_t left = g.n - t0;
+    const int cnt = (int)(left < g.own ? left : g.own);
+    T u[M];
+    window_load<T, M>(u, g.in, g.n, x0);
+    auto each = [&](int j) {
+        if constexpr (ALL)
+            window_store<T, M>(u, g.out + j * g.n, t0, g.halo, cnt);
+    };
+    if constexpr (is_ks<S>) {
+        ks_advance<S, M>(u, g, x0, each);
+    } else if constexpr (has_faces<S>::value) {
+        static_assert(!ALL, "the adjoint's stencils only");
+        euler_advance<S, M>(u, g);
+    } else {
+        heat_advance<S, M>(u, g, each);
+    }
+    if constexpr (!ALL)
+        window_store<T, M>(u, g.out, t0, g.halo, cnt);
 }
 
 // Workgroups are dealt to the eight XCDs in turn: workgroup b of a launch of
@@ -414,12 +435,13 @@ __device__ __forceinline__ unsigned xcd_run(unsigned b, unsigned count)
 
 // One stage of one field: workgroup = one wave = one tile.  Neighbouring tiles
 // run on one XCD, so that the halos they share are read through one L2.
-template <class S, int M>
+// ALL: of every step's field (window_tile).
+template <class S, int M, bool ALL>
 __global__ __launch_bounds__(64) void window_kernel(WindowArgs<S> g)
 {
     const unsigned tile = xcd_run(blockIdx.x, (unsigned)g.tiles);
     if (tile < (unsigned)g.tiles)
-        window_tile<S, M>(g, tile);
+        window_tile<S, M, ALL>(g, tile);
 }
 
 // ------------------------------------------------------------------ batch
@@ -480,6 +502,140 @@ __global__ __launch_bounds__(64) void window_batch_kernel(WindowBatchArgs<S> b)
         g.guard = b.stage == 0 ? b.guard : 0;
     }
     window_tile<S, M>(g, (unsigned)task.tile);
+}
+
+// ---------------------------------------------------------------- adjoint
+// The discrete adjoint on windows: a stage takes the cotangent field of step
+// first + steps back to step `first`, each step by the transposed
+// sub-timesteps (S::adj) on the forward field the forward pass kept of that
+// step, whose middle level (KS: v) is recomputed in registers.  A window's
+// cotangents go wrong from its ends by the stencil's radius per step; the
+// recomputed v by three columns whatever the depth, which its first step
+// passes on: the halo is radius x steps, plus two for KS.
+//
+// What bounds it: the chain of a step, about 60 operations a point with 28
+// DPP moves, one wave per SIMD on the grids this is used for.  Keeping every
+// step's field (8 bytes a point and step; the lane-frame stages kept 6) costs
+// no recomputation beyond v, no LDS and no halo for forward values: against
+// swept_adjoint_kernel's stages of 8 KS steps (forward recomputed, then
+// reversed, two rows a level) 2.2 -> 0.7 us a step at 2^16 points.
+template <class S>
+struct WindowAdjArgs {
+    const typename S::T* u0;      // field of step 0
+    const typename S::T* kept;    // field of step j >= kept0 at kept + (j - kept0)*n
+    int64_t kept0;
+    const typename S::T* in;      // cotangent of step first + steps (null: zero)
+    typename S::T* out;           // cotangent of step `first`
+    int64_t n, own;
+    int tiles, halo, steps;
+    int seed;                     // `in` is the objective's cotangent of the final field
+    int64_t first;                // time step of `out`
+    int64_t win_first;            // first time step of the objective's window
+    typename S::T two_w;          // 2 * objective weight
+    typename S::Consts c;
+};
+
+// the transposed sub-timestep PH of all points of the window; k: the forward
+// values it reads
+template <class S, int PH, int M>
+__device__ __forceinline__ void adj_phase(typename S::Ad (&a)[M], const typename S::Kept (&k)[M],
+                                          const typename S::Consts& c)
+{
+    using Ad = typename S::Ad;
+    using Kept = typename S::Kept;
+    Ad prev = dpp_record<kWaveShr1>(a[M - 1]);
+    const Ad right = dpp_record<kWaveShl1>(a[0]);
+    const Kept kl = dpp_record<kWaveShr1>(k[M - 1]), kr = dpp_record<kWaveShl1>(k[0]);
+#pragma unroll
+    for (int q = 0; q < M; ++q) {
+        const Ad cur = a[q];
+        a[q] = S::template adj<PH>(prev, cur, q + 1 < M ? a[q + 1 < M ? q + 1 : 0] : right,
+                                   q > 0 ? k[q > 0 ? q - 1 : 0] : kl, k[q],
+                                   q + 1 < M ? k[q + 1 < M ? q + 1 : 0] : kr, c);
+        prev = cur;
+    }
+}
+
+template <class S, int M>
+__global__ __launch_bounds__(64) void window_adjoint_kernel(WindowAdjArgs<S> g)
+{
+    using T = typename S::T;
+    using Ad = typename S::Ad;
+    using Kept = typename S::Kept;
+    const unsigned tile = xcd_run(blockIdx.x, (unsigned)g.tiles);
+    if (tile >= (unsigned)g.tiles)
+        return;
+    const int64_t t0 = (int64_t)tile * g.own;
+    const int64_t x0 = t0 - g.halo;
+    const int64_t left = g.n - t0;
+    const int cnt = (int)(left < g.own ? left : g.own);
+    auto field = [&](int64_t j) { return j == 0 ? g.u0 : g.kept + (j - g.kept0) * g.n; };
+    const int64_t last = g.first + g.steps;
+    T lam[M], f[M];
+    if (g.in != nullptr) {
+        window_load<T, M>(lam, g.in, g.n, x0);
+    } else {
+#pragma unroll
+        for (int q = 0; q < M; ++q)
+            lam[q] = T(0);
+    }
+    Ad a[M];
+    if (g.seed != 0 && last >= g.win_first) {
+        window_load<T, M>(f, field(last), g.n, x0);
+#pragma unroll
+        for (int q = 0; q < M; ++q)
+            a[q] = S::seed(lam[q], g.two_w, f[q], true);
+    } else {
+#pragma unroll
+        for (int q = 0; q < M; ++q)
+            a[q] = S::seed(lam[q], g.two_w, T(0), false);
+    }
+    // a step's forward values: for KS every step's, for heat those of the
+    // window (its transposed step reads none)
+    constexpr bool kAlways = S::NPHASE != 1;
+    int64_t j = last - 1;
+    if (g.steps > 0 && (kAlways || j >= g.win_first))
+        window_load<T, M>(f, field(j), g.n, x0);
+    for (; j >= g.first; --j) {
+        T fn[M];   // the next step's field, on its way while this one is computed
+#pragma unroll
+        for (int q = 0; q < M; ++q)
+            fn[q] = T(0);
+        if (j > g.first && (kAlways || j - 1 >= g.win_first))
+            window_load<T, M>(fn, field(j - 1), g.n, x0);
+        Kept k[M];
+#pragma unroll
+        for (int q = 0; q < M; ++q)
+            k[q] = f[q];
+        if constexpr (S::NPHASE == 4) {
+            typename S::Pt P[M];
+#pragma unroll
+            for (int q = 0; q < M; ++q)
+                P[q] = S::from_field(f[q]);
+            window_phase<S, 0, M>(P, g.c);
+            window_phase<S, 1, M>(P, g.c);
+            Kept kv[M];
+#pragma unroll
+            for (int q = 0; q < M; ++q)
+                kv[q] = S::template keep<3>(P[q]);
+            adj_phase<S, 3, M>(a, kv, g.c);
+            adj_phase<S, 2, M>(a, kv, g.c);
+            adj_phase<S, 1, M>(a, k, g.c);
+        }
+        adj_phase<S, 0, M>(a, k, g.c);
+        if (j >= g.win_first) {
+#pragma unroll
+            for (int q = 0; q < M; ++q)
+                a[q] = S::source(a[q], k[q], g.two_w);
+        }
+#pragma unroll
+        for (int q = 0; q < M; ++q)
+            f[q] = fn[q];
+    }
+#pragma unroll
+    for (int q = 0; q < M; ++q)
+        lam[q] = S::grad(a[q]);
+    window_store<T, M>(lam, g.out, t0, g.halo, cnt);
 }
 
 }  // namespace swept

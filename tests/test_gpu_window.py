@@ -187,6 +187,48 @@ def test_batch_of_nothing(sw):
     assert all(bool((u == 1).all()) for u in us)
 
 
+@pytest.mark.parametrize("n,nsteps,first", [
+    (8, 1, 2), (8, 3, 0), (64, 2, 2), (64, 40, 41), (130, 65, 30), (1000, 33, 1), (4098, 120, 121),
+    (20000, 50, 50),
+])
+@pytest.mark.parametrize("stencil", ["heat", "ks"])
+@pytest.mark.parametrize("with_cot", [False, True])
+def test_adjoint_bitwise(sw, oracle_mod, stencil, n, nsteps, first, with_cot):
+    """Gradients on windows: no window, one that starts at step 0, inside and
+    at the last step, with and without a final cotangent, rings smaller than
+    the halo."""
+    import torch
+    u0 = workloads.white_noise(n, seed=n) if stencil == "heat" else \
+        5 * workloads.smoothed_noise(n, seed=n)
+    cot = workloads.white_noise(n, seed=1) if with_cot else None
+    par = [0.3] if stencil == "heat" else KS_P
+    g = sw.adjoint(torch.from_numpy(u0).cuda(), nsteps, stencil, par, window_first=first,
+                   window_weight=0.01, cot_final=None if cot is None else torch.from_numpy(cot).cuda())
+    torch.cuda.synchronize()
+    oracle = oracle_mod.heat_adjoint if stencil == "heat" else oracle_mod.ks_adjoint
+    assert same_bits(g.cpu().numpy(), oracle(u0, nsteps, *par, first, 0.01, cot))
+
+
+@pytest.mark.parametrize("stencil,n,nsteps,first", [
+    ("heat", 1000, 40, 30), ("ks", 4099, 2100, 2), ("ks_fma", 300, 9, 0), ("heat_fma", 65536, 400, 100),
+])
+def test_objective_bits_do_not_depend_on_the_schedule(sw, stencil, n, nsteps, first):
+    """The sums over steps kept by windows equal those formed one naive step at
+    a time (a tile width asks for the swept and naive schedules)."""
+    import torch
+    u0 = torch.from_numpy(workloads.smoothed_noise(n, seed=3)).cuda()
+    par = [0.3] if stencil.startswith("heat") else KS_P
+    kw = dict(window_first=first, window_weight=0.5, cot_final=u0.flip(0).contiguous())
+    a = sw.objective(u0, nsteps, stencil, par, **kw)
+    sw.set_tuning(0, 0, sw.MODE_NAIVE)
+    try:
+        b = sw.objective(u0, nsteps, stencil, par, **kw)
+    finally:
+        sw.set_tuning(0, 0, sw.MODE_AUTO)
+    torch.cuda.synchronize()
+    assert float(a) == float(b)
+
+
 @pytest.mark.parametrize("n,W", [(4096, 128), (65536, 1024)])
 def test_profiled_stages_are_reported(sw, n, W):
     import torch
