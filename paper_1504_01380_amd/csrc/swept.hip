@@ -1648,34 +1648,35 @@ struct WindowPlan {
     int64_t own = 0;       // points per tile
     int64_t tiles = 0;
     int64_t h = 0;         // most time steps of a stage
+    int halo = 0;          // points on either side of the owned ones
     int64_t stages = 0;
     double cost = 1e300;   // predicted time, ns
 };
 
-// Time of one row (one time step of one window of 64*M points), fitted to
-// sweeps of M and h on MI355X (heat with three operations a point: a lone
-// wave 30 + 4.9 M ns over M = 2..48 at 4096 points; at 2^24 points a SIMD
-// issues 4.4 cycles an operation whatever the number of its waves).
+// Time of one row (one time step of one window of 64*M points) of a wave
+// alone on its SIMD, fitted to sweeps of M and h on MI355X: heat (three
+// operations a point) 17 + 5.6 M ns over M = 2..20, KS (21) 35 + 41 M over
+// M = 2..20, Euler (490) 0.15 + 1.08 M us over M = 1..6.
 struct WindowCost {
-    double lat;      // ns a row of a lone wave takes beside its operations
+    double lat;      // ns a row takes beside its points
     double per;      // ns per point and lane
 };
 
 WindowCost window_cost(int id, int ops)
 {
     switch (base_id(id)) {
-    case SWEPT_HEAT_F32: return WindowCost{30.0, 1.2 * ops};
-    case SWEPT_KS_F64: return WindowCost{90.0, 1.63 * ops};
-    case SWEPT_EULER_F64: return WindowCost{150.0, 1.75 * ops};
-    default: return WindowCost{30.0, 1.63 * ops};
+    case SWEPT_HEAT_F32: return WindowCost{17.0, 1.4 * ops};
+    case SWEPT_KS_F64: return WindowCost{35.0, 1.95 * ops};
+    case SWEPT_EULER_F64: return WindowCost{150.0, 2.2 * ops};
+    default: return WindowCost{17.0, 1.87 * ops};
     }
 }
 
 size_t field_bytes(int id);
 
 // points per lane the window kernels are built for
-constexpr int kWindowHeat[] = {2, 3, 4, 6, 8, 12, 16, 24, 32, 48};
-constexpr int kWindowKs[] = {2, 3, 4, 6, 8, 10, 12, 14, 16, 18, 20, 24};
+constexpr int kWindowHeat[] = {2, 3, 4, 6, 8, 12, 18, 20, 24, 32, 48};
+constexpr int kWindowKs[] = {2, 3, 4, 5, 6, 8, 10, 12, 18, 20, 24};
 constexpr int kWindowEuler[] = {1, 2, 3, 4, 6};
 constexpr int kWindowAdj[] = {2, 3, 4, 6, 8};    // the adjoint, and stages that keep every step
 
@@ -1688,13 +1689,14 @@ struct WindowShape {
     int radius, extra;
     double bytes;
     WindowCost cost;
+    bool lanes = false;   // owned parts of whole lanes (stages that store every step)
 };
 
 template <size_t N>
 WindowShape window_shape(const int (&sizes)[N], int id, int ops)
 {
     return WindowShape{sizes, (int)N, substeps_of(id), 0, (double)field_bytes(id),
-                       window_cost(id, ops)};
+                       window_cost(id, ops), false};
 }
 
 [[maybe_unused]] WindowShape window_shape(int id, int ops)
@@ -1707,13 +1709,15 @@ WindowShape window_shape(const int (&sizes)[N], int id, int ops)
 }
 
 // The window size and stage depth of least predicted time.  A stage costs a
-// launch and its loads and stores (about 2 us, and the field's bytes in and
-// out at 9 TB/s, partly hidden) plus h rows; 1024 SIMDs share the tiles, and
-// a row takes the longer of a lone wave's latency and the issue time of all
-// the waves of a SIMD.  Deep stages spread the launch, wide windows the halo;
-// few tiles (small grids) want small windows, whose rows are short.
-[[maybe_unused]] WindowPlan window_plan(const WindowShape& shape, int64_t n, int64_t nsteps,
-                                        int64_t hmax)
+// launch (2.2 us with the first load and the last store), the field's bytes in
+// and out (4.5 us in all at 2^20 binary64 points, where all waves move data at
+// the same time: 7 TB/s; half hidden by other waves' rows once a SIMD holds
+// several), and h rows; 1024 SIMDs share the tiles, and a row takes the longer
+// of a lone wave's time and the issue time of all the waves of a SIMD (a lone
+// wave issues at 0.88 of the rate of several).  Deep stages spread the launch,
+// wide windows the halo; few tiles (small grids) want small windows, whose
+// rows are short.
+[[maybe_unused]] WindowPlan window_plan(const WindowShape& shape, int64_t n, int64_t nsteps)
 {
     const int R = shape.radius;
     const WindowCost c = shape.cost;
@@ -1723,7 +1727,7 @@ WindowShape window_shape(const int (&sizes)[N], int id, int ops)
         const int64_t W = 64 * M;
         int64_t last = 0;
         for (int f = 1; f <= 14; ++f) {
-            int64_t h = std::min({W * f / (32 * R), hmax, (nsteps + 1) / 2});
+            int64_t h = std::min(W * f / (32 * R), (nsteps + 1) / 2);
             if (h < 1 || h == last)
                 continue;
             last = h;
@@ -1731,20 +1735,27 @@ WindowShape window_shape(const int (&sizes)[N], int id, int ops)
             p.stages = (nsteps + h - 1) / h;
             p.stages += p.stages & 1;
             p.h = (nsteps + p.stages - 1) / p.stages;
-            const int64_t room = W - 2 * (R * p.h + shape.extra);
+            // halos and owned parts are multiples of 8 and 16 points (whole lines;
+            // misaligned ones took 24.8 us a stage instead of 20 at 2^20 + 1
+            // points), or of the lanes' M points
+            const int64_t grain = shape.lanes ? M : 8, own_grain = shape.lanes ? M : 16;
+            p.halo = (int)((R * p.h + shape.extra + grain - 1) / grain * grain);
+            const int64_t room = (W - 2 * p.halo) / own_grain * own_grain;
+            if (room < own_grain)
+                continue;
             p.M = M;
             p.tiles = (n + room - 1) / room;
             if (p.tiles > (int64_t(1) << 30))
                 continue;
-            // equal tiles, starting on 64-byte lines where there is room for that
             p.own = (n + p.tiles - 1) / p.tiles;
-            p.own = std::min(room, (p.own + 15) / 16 * 16);
+            p.own = (p.own + own_grain - 1) / own_grain * own_grain;
             p.tiles = (n + p.own - 1) / p.own;
             const double w = (double)p.tiles / 1024.0;
             const double waves = w <= 8.0 ? std::ceil(w) : w + 0.5;
-            const double row = std::max(c.lat + c.per * M, waves * (5.0 + c.per * M));
-            const double mem = (double)n * shape.bytes * (1.0 + (double)W / (double)p.own) / 9000.0;
-            p.cost = (double)p.stages * (2000.0 + mem + (double)p.h * row);
+            const double row = std::max(c.lat + c.per * M, waves * (5.0 + 0.88 * c.per * M));
+            const double mem = (double)n * shape.bytes * (1.0 + (double)W / (double)p.own) /
+                               (w > 2.0 ? 14000.0 : 7000.0);
+            p.cost = (double)p.stages * (2200.0 + mem + (double)p.h * row);
             if (p.cost < best.cost)
                 best = p;
         }
@@ -1775,11 +1786,11 @@ template <class S>
 void launch_window(const WindowArgs<S>& a, int M, hipStream_t st)
 {
     if constexpr (is_ks<S>)
-        launch_window_of<S>(a, M, st, std::integer_sequence<int, 2, 3, 4, 6, 8, 10, 12, 14, 16, 18, 20, 24>{});
+        launch_window_of<S>(a, M, st, std::integer_sequence<int, 2, 3, 4, 5, 6, 8, 10, 12, 18, 20, 24>{});
     else if constexpr (has_faces<S>::value)
         launch_window_of<S>(a, M, st, std::integer_sequence<int, 1, 2, 3, 4, 6>{});
     else
-        launch_window_of<S>(a, M, st, std::integer_sequence<int, 2, 3, 4, 6, 8, 12, 16, 24, 32, 48>{});
+        launch_window_of<S>(a, M, st, std::integer_sequence<int, 2, 3, 4, 6, 8, 12, 18, 20, 24, 32, 48>{});
 }
 
 // r = 2^-e with e >= 1: e; else 0
@@ -1798,8 +1809,8 @@ struct WindowForm {
     bool fused = false;
     int e = 0;          // heat: exact-product form for r = 2^-e (0: no)
     bool exact = false; // KS: exact-product form
+    int rows = 0;       // heat: rows between two looks at the smallest value
     int ops = 5;        // operations per point of the form expected
-    int64_t hmax = int64_t(1) << 40;
 };
 
 template <class S>
@@ -1826,13 +1837,13 @@ WindowForm<S> window_form(const typename S::Consts& c, int64_t L)
                   L <= kFusedMaxLevels<T>;
         if (f.fused) {
             f.ops = 4;
-            // a stage of h steps may raise the smallest value allowed to
-            // 2^(emin + e*h): 2^-46 in binary32, 2^-200 in binary64
+            // h rows need values of at least 2^(emin + e*h): as many as raise
+            // that to 2^-46 in binary32, 2^-200 in binary64
             const int room = -(std::numeric_limits<T>::min_exponent - 1) - (sizeof(T) == 8 ? 200 : 46);
             f.e = pow2_exponent(c.r);
             if (f.e > 0 && room / f.e >= 16) {
                 f.ops = 3;
-                f.hmax = room / f.e;
+                f.rows = room / f.e;
             } else {
                 f.e = 0;
             }
@@ -1866,7 +1877,7 @@ WindowArgs<S> window_args(const WindowPlan& p, const WindowForm<S>& form, int64_
     a.own = p.own;
     a.tiles = (int)p.tiles;
     a.steps = (int)steps;
-    a.halo = a.steps * S::NPHASE;
+    a.halo = p.halo;
     a.c = c;
     a.fused = form.fused;
     if constexpr (is_ks<S>) {
@@ -1874,8 +1885,9 @@ WindowArgs<S> window_args(const WindowPlan& p, const WindowForm<S>& form, int64_
         a.tiny = form.exact ? std::ldexp(1.0, -400) : 0.0;
     } else if constexpr (!has_faces<S>::value) {
         a.big = std::numeric_limits<T>::max() / (first ? 16 : 8);
+        a.rows = std::min(a.steps, form.rows);
         a.tiny = form.e > 0 ? std::ldexp(T(1), std::numeric_limits<T>::min_exponent - 1 +
-                                                   form.e * a.steps)
+                                                   form.e * a.rows)
                             : T(0);
     }
     return a;
@@ -1887,7 +1899,7 @@ int window_stages(const typename S::T* in, typename S::T* out, typename S::T* sp
                   int64_t nsteps, int id, const typename S::Consts& c, const WindowForm<S>& form,
                   unsigned long long guard)
 {
-    const WindowPlan p = window_plan(window_shape(id, form.ops), nx, nsteps, form.hmax);
+    const WindowPlan p = window_plan(window_shape(id, form.ops), nx, nsteps);
     if (p.M == 0)
         return fail(SWEPT_EUNSUPPORTED, "nx = %lld is too long", (long long)nx);
     if (g_ctx.profiling) {
@@ -1936,7 +1948,9 @@ int window_keep(const typename S::T* in, typename S::T* kept, int64_t nx, int64_
 {
     if (nsteps <= 0)
         return SWEPT_OK;
-    const WindowPlan p = window_plan(window_shape(kWindowAdj, id, form.ops), nx, nsteps, form.hmax);
+    WindowShape shape = window_shape(kWindowAdj, id, form.ops);
+    shape.lanes = true;
+    const WindowPlan p = window_plan(shape, nx, nsteps);
     if (p.M == 0)
         return fail(SWEPT_EUNSUPPORTED, "nx = %lld is too long", (long long)nx);
     for (int64_t s = 0; s < p.stages; ++s) {
@@ -2030,7 +2044,7 @@ int run_window_adjoint(const typename S::T* u0, typename S::T* grad, int64_t nx,
         WindowShape shape = window_shape(kWindowAdj, id, ks ? kAdjOps : 6);
         if (ks)
             shape.extra = 2;
-        const WindowPlan p = window_plan(shape, nx, std::max<int64_t>(total, 1), int64_t(1) << 40);
+        const WindowPlan p = window_plan(shape, nx, std::max<int64_t>(total, 1));
         if (p.M == 0)
             return fail(SWEPT_EUNSUPPORTED, "nx = %lld is too long", (long long)nx);
         WindowAdjArgs<S> a{};
@@ -2049,7 +2063,7 @@ int run_window_adjoint(const typename S::T* u0, typename S::T* grad, int64_t nx,
             if (upto == done && (total > 0 || s > 0))
                 continue;   // no steps, and not the seed alone
             a.steps = (int)(upto - done);
-            a.halo = a.steps * S::NPHASE + shape.extra;
+            a.halo = p.halo;
             a.seed = done == 0;
             a.first = nsteps - upto;
             a.in = in;
@@ -2114,10 +2128,12 @@ constexpr int kWindowBatchKs[] = {4, 8, 12, 18};
             const int64_t h = std::min({W * f / (32 * R), hmax, (smax + 1) / 2});
             if (h < 1)
                 continue;
-            const double room = (double)(W - 2 * R * h);
+            const double room = (double)((W - 2 * ((R * h + 7) / 8 * 8)) / 16 * 16);
+            if (room < 16)
+                continue;
             const double stages = std::ceil((double)smax / (double)h);
             const double rows = (sns + (double)h * sn) / room + 0.5 * (ss + count * (double)h);
-            const double full = rows * (5.0 + c.per * M) / 1024.0 +
+            const double full = rows * (5.0 + 0.88 * c.per * M) / 1024.0 +
                                 stages * 0.5 * (double)h * c.per * M;
             const double alone = stages * (double)h * (c.lat + c.per * M);
             const double mem = 16.0 * (sns / (double)h + sn) / 5000.0;
@@ -2239,10 +2255,13 @@ struct WindowBatch {
             sns += (double)nx[j] * (double)nsteps[j];
             smax = std::max(smax, nsteps[j]);
             ops = std::max(ops, forms[q].ops);
-            hmax = std::min(hmax, forms[q].hmax);
+            if (forms[q].rows > 0)   // one look at the smallest value a stage
+                hmax = std::min<int64_t>(hmax, forms[q].rows);
         }
         plan = window_batch_plan(id, ops, hmax, sn, ss, sns, (double)js.size(), smax);
-        const int64_t room = 64 * plan.M - 2 * S::NPHASE * plan.h;
+        const int64_t halo = (S::NPHASE * plan.h + 7) / 8 * 8;
+        const int64_t room = (64 * plan.M - 2 * halo) / 16 * 16;
+        args.halo = (int)halo;
         inst.resize(js.size());
         stages.resize(js.size());
         std::vector<int64_t> tiles(js.size());
@@ -2255,7 +2274,7 @@ struct WindowBatch {
             const int64_t t = (nx[j] + room - 1) / room;
             I.u = static_cast<typename S::T*>(u[j]);
             I.n = nx[j];
-            I.own = (int)std::min(room, ((nx[j] + t - 1) / t + 15) / 16 * 16);
+            I.own = (int)(((nx[j] + t - 1) / t + 15) / 16 * 16);
             I.base = (int)(nsteps[j] / st);
             I.rem = (int)(nsteps[j] % st);
             I.fused = forms[q].fused;
@@ -2410,8 +2429,8 @@ int run_window_batch(void* const* u, const int64_t* nx, const int64_t* nsteps, c
 // the swept one 48 a point for every k/4 KS steps, 16 for every k heat steps).
 [[maybe_unused]] bool use_window_adjoint(int64_t nx, int64_t nsteps, int id, int64_t win_first)
 {
-    if (!kWindows || nsteps == 0 || g_ctx.mode != SWEPT_MODE_AUTO || g_ctx.tile_w != 0 ||
-        g_ctx.ppl != 0 || (id != SWEPT_HEAT_F64 && id != SWEPT_KS_F64))
+    if (!kWindows || nsteps == 0 || nx >= (int64_t(1) << 28) || g_ctx.mode != SWEPT_MODE_AUTO ||
+        g_ctx.tile_w != 0 || g_ctx.ppl != 0 || (id != SWEPT_HEAT_F64 && id != SWEPT_KS_F64))
         return false;
     const bool ks = id == SWEPT_KS_F64;
     const int64_t k = ks ? adjoint_depth<KSF64>(nx, 0) : adjoint_depth<HeatF64>(nx, 0);

@@ -51,6 +51,7 @@ struct WindowArgs {
     int fused;                  // 0: the operations as written only
     WindowBound<S> big;         // largest |u| of the fused forms
     WindowBound<S> tiny;        // smallest |u| of the exact-product form (0: not allowed)
+    int rows;                   // heat: rows `tiny` is good for
     unsigned long long guard;   // heat: the call's id on its first stage (marks the call), else 0
 };
 
@@ -86,11 +87,11 @@ __device__ __forceinline__ typename S::T heat_point(typename S::T u, typename S:
 // update cost one v_mov_b64 per point, 19% of the row).
 // each(j): called with the window at row j = 0, 1, ... done.
 template <class S, int M, class Each>
-__device__ __forceinline__ void heat_rows(typename S::T (&u)[M], int rows,
+__device__ __forceinline__ void heat_rows(typename S::T (&u)[M], int first, int rows,
                                           const typename S::Consts& k, Each&& each)
 {
     using T = typename S::T;
-    for (int j = 0; j < rows; ++j) {
+    auto row = [&](int j) {
         const T left = dpp_record<kWaveShr1>(u[M - 1]);
         const T right = dpp_record<kWaveShl1>(u[0]);
         T s = left + (M > 1 ? u[M > 1 ? 1 : 0] : right);
@@ -103,7 +104,18 @@ __device__ __forceinline__ void heat_rows(typename S::T (&u)[M], int rows,
             s = sn;
         }
         each(j);
+    };
+    int j = first;
+    if constexpr (M <= 8) {   // short rows: the loop's own instructions are a fifth of them
+        for (; j + 4 <= rows; j += 4) {
+            row(j);
+            row(j + 1);
+            row(j + 2);
+            row(j + 3);
+        }
     }
+    for (; j < rows; ++j)
+        row(j);
 }
 
 // Heat's evaluation of a window for one stage.  The conditions of the fused
@@ -112,8 +124,9 @@ __device__ __forceinline__ void heat_rows(typename S::T (&u)[M], int rows,
 // `big` (HeatLap: with 0 <= r <= 1/2 the values cannot come near the
 // overflow of 2u inside a stage; the host passes MAX/16 for the initial field
 // and MAX/8, which the run-length bound keeps out of reach, afterwards), and
-// for the exact-product form no nonzero |u| below `tiny`.  A wave decides for
-// itself; all forms give the same bits.
+// for the exact-product form no nonzero |u| below `tiny`, which holds for
+// `rows` rows: a deeper stage (binary32) looks again after each of them.  A
+// wave decides for itself; all forms give the same bits.
 template <class S, int M, class Each>
 __device__ __forceinline__ void heat_advance(typename S::T (&u)[M], const WindowArgs<S>& g,
                                              Each&& each)
@@ -121,25 +134,52 @@ __device__ __forceinline__ void heat_advance(typename S::T (&u)[M], const Window
     using T = typename S::T;
     if constexpr (has_fused_form<S>) {
         if (g.fused != 0) {
-            bool bad = false, sub = g.tiny == T(0);
+            // one maximum and one minimum a point settle nearly every window;
+            // infinities and zeros, which are allowed, take the exact look
+            T mx = T(0);
 #pragma unroll
-            for (int q = 0; q < M; ++q) {
-                const T a = __builtin_fabs(u[q]);
-                bad = bad || (a > g.big && __builtin_isfinite(a));
-                sub = sub || (a < g.tiny && a != T(0));
+            for (int q = 0; q < M; ++q)
+                mx = __builtin_fmax(mx, __builtin_fabs(u[q]));
+            bool bad = mx > g.big;
+            if (__any(bad)) {
+                bad = false;
+#pragma unroll
+                for (int q = 0; q < M; ++q) {
+                    const T a = __builtin_fabs(u[q]);
+                    bad = bad || (a > g.big && __builtin_isfinite(a));
+                }
             }
             if (!__any(bad)) {
-                if (!__any(sub))
-                    heat_rows<HeatExact<T>, M>(u, g.steps, g.c, each);
-                else
-                    heat_rows<HeatLap<T>, M>(u, g.steps, g.c, each);
+                int j = 0;
+                while (g.tiny > T(0) && j < g.steps) {
+                    T mn = __builtin_fabs(u[0]);
+#pragma unroll
+                    for (int q = 1; q < M; ++q)
+                        mn = __builtin_fmin(mn, __builtin_fabs(u[q]));
+                    bool sub = mn < g.tiny;
+                    if (__any(sub)) {
+                        sub = false;
+#pragma unroll
+                        for (int q = 0; q < M; ++q) {
+                            const T a = __builtin_fabs(u[q]);
+                            sub = sub || (a < g.tiny && a != T(0));
+                        }
+                        if (__any(sub))
+                            break;
+                    }
+                    const int upto = min(j + g.rows, g.steps);
+                    heat_rows<HeatExact<T>, M>(u, j, upto, g.c, each);
+                    j = upto;
+                }
+                if (j < g.steps)
+                    heat_rows<HeatLap<T>, M>(u, j, g.steps, g.c, each);
                 return;
             }
             if (g.guard != 0 && threadIdx.x == 0)
                 atomicMax(&g_form_mark, g.guard);
         }
     }
-    heat_rows<S, M>(u, g.steps, g.c, each);
+    heat_rows<S, M>(u, 0, g.steps, g.c, each);
 }
 
 // ------------------------------------------------------------------- KS
@@ -320,6 +360,41 @@ __device__ __forceinline__ void euler_advance(typename S::T (&u)[M], const Windo
         u[q] = S::to_field(P[q]);
 }
 
+// How a window passes between HBM and the lanes' blocks of M points.  Reading a
+// block per lane straight from HBM spreads every 16-byte access of a wave over
+// 64 cache lines.  Where one wave fills its SIMD (blocks of 128 to 208 bytes,
+// the windows of about 2^20 points) nothing hides that: a stage of heat
+// (M = 20) took 8 us beside its rows, 4.5 us when the wave reads and writes
+// 16-byte quads in order (1 KB an instruction) and turns them through LDS:
+// lane l's block starts at quad l*(kQuads + kPad), kPad making the stride odd
+// against bank conflicts.  Smaller blocks spread less, and with several waves
+// on a SIMD (larger blocks, at 2^24 points) the turn costs more than it saves
+// (heat M = 48: 219 us a stage without, 237 with it).
+template <class T, int M>
+struct WindowTurn {
+    static constexpr int kBytes = M * (int)sizeof(T);
+    static constexpr bool kUse =
+        16 % sizeof(T) == 0 && kBytes >= 128 && kBytes <= 208 && kBytes % 16 == 0;
+    static constexpr int kQuads = kBytes / 16;
+    static constexpr int kPad = kQuads % 2 == 0 ? 1 : 0;
+};
+struct alignas(16) Quad {
+    unsigned w[4];
+};
+// a quad of field values wherever it starts (values are aligned to themselves)
+template <class T>
+struct alignas(sizeof(T) % 8 == 0 ? 8 : 4) LooseQuad {
+    unsigned w[4];
+};
+
+template <class T, int M>
+__device__ __forceinline__ Quad* window_lds()
+{
+    using Turn = WindowTurn<T, M>;
+    __shared__ Quad buf[64 * (Turn::kQuads + Turn::kPad)];
+    return buf;
+}
+
 // A lane's M points of the window that starts at point x0 of the ring
 // (-n < x0 < n where n >= 64*M).
 template <class T, int M>
@@ -328,10 +403,32 @@ __device__ __forceinline__ void window_load(T (&u)[M], const T* in, int64_t n, i
     constexpr int W = 64 * M;
     const int lane = threadIdx.x;
     if (x0 >= 0 && x0 + W <= n) {
-        const T* p = in + (x0 + lane * M);
+        if constexpr (WindowTurn<T, M>::kUse) {
+            constexpr int Q = WindowTurn<T, M>::kQuads, pad = WindowTurn<T, M>::kPad;
+            const auto* p = reinterpret_cast<const LooseQuad<T>*>(in + x0);
+            Quad* lds = window_lds<T, M>();
+            LooseQuad<T> r[Q];   // all loads in flight before the first is turned
 #pragma unroll
-        for (int q = 0; q < M; ++q)
-            u[q] = p[q];
+            for (int i = 0; i < Q; ++i)
+                r[i] = p[i * 64 + lane];
+#pragma unroll
+            for (int i = 0; i < Q; ++i) {
+                const int e = i * 64 + lane;
+                __builtin_memcpy(&lds[e + pad * (e / Q)], &r[i], 16);
+            }
+            __syncthreads();
+            Quad w[Q];
+#pragma unroll
+            for (int i = 0; i < Q; ++i)
+                w[i] = lds[lane * (Q + pad) + i];
+            __builtin_memcpy(u, w, sizeof(u));
+            __syncthreads();
+        } else {
+            const T* p = in + (x0 + lane * M);
+#pragma unroll
+            for (int q = 0; q < M; ++q)
+                u[q] = p[q];
+        }
     } else {   // the window crosses the ring's seam, perhaps more than once
         int64_t x = x0 + lane * M;
         if (n >= W) {
@@ -355,16 +452,16 @@ __device__ __forceinline__ void ks_advance(double (&u)[M], const WindowArgs<S>& 
                                            Each&& each)
 {
     if (g.fused != 0) {
-        bool in = true, small = g.tiny == 0.0;
+        // (a NaN passes as itself: its results are NaNs in every form)
+        double mx = 0.0, mn = __builtin_fabs(u[0]);
 #pragma unroll
         for (int q = 0; q < M; ++q) {
-            const double a = __builtin_fabs(u[q]);
-            in = in && a <= g.big;
-            small = small || !(a >= g.tiny);
+            mx = __builtin_fmax(mx, __builtin_fabs(u[q]));
+            mn = __builtin_fmin(mn, __builtin_fabs(u[q]));
         }
-        if (__all(in)) {
+        if (__all(mx <= g.big)) {
             bool ok;
-            if (!__any(small))
+            if (g.tiny != 0.0 && !__any(mn < g.tiny))
                 ok = ks_rows<S, kKsExact, M>(u, g.steps, g.c, each);
             else if constexpr (!is_ks_fma<S>)
                 ok = ks_rows<S, kKsLap, M>(u, g.steps, g.c, each);
@@ -382,17 +479,48 @@ __device__ __forceinline__ void ks_advance(double (&u)[M], const WindowArgs<S>& 
 template <class T, int M>
 __device__ __forceinline__ void window_store(const T (&u)[M], T* out, int64_t t0, int halo, int cnt)
 {
-    const int c0 = (int)threadIdx.x * M - halo;   // this lane's first column among the owned
-    T* o = out + (t0 + c0);
-    if (c0 >= 0 && c0 + M <= cnt) {
+    const int lane = threadIdx.x;
+    T* base = out + (t0 - halo);   // the window's column 0
+    if constexpr (WindowTurn<T, M>::kUse) {
+        constexpr int Q = WindowTurn<T, M>::kQuads, pad = WindowTurn<T, M>::kPad;
+        constexpr int V = 16 / (int)sizeof(T);
+        Quad* lds = window_lds<T, M>();
+        Quad w[Q];
+        __builtin_memcpy(w, u, sizeof(u));
 #pragma unroll
-        for (int q = 0; q < M; ++q)
-            o[q] = u[q];
+        for (int i = 0; i < Q; ++i)
+            lds[lane * (Q + pad) + i] = w[i];
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < Q; ++i) {
+            const int e = i * 64 + lane;
+            T v[V];
+            __builtin_memcpy(v, &lds[e + pad * (e / Q)], 16);
+            const int c = e * V - halo;   // the quad's first column among the owned
+            if (c >= 0 && c + V <= cnt) {
+                LooseQuad<T> x;
+                __builtin_memcpy(&x, v, 16);
+                *reinterpret_cast<LooseQuad<T>*>(base + e * V) = x;
+            } else {
+#pragma unroll
+                for (int q = 0; q < V; ++q)
+                    if (c + q >= 0 && c + q < cnt)
+                        base[e * V + q] = v[q];
+            }
+        }
     } else {
+        const int c0 = lane * M - halo;   // this lane's first column among the owned
+        T* o = base + lane * M;
+        if (c0 >= 0 && c0 + M <= cnt) {
 #pragma unroll
-        for (int q = 0; q < M; ++q)
-            if (c0 + q >= 0 && c0 + q < cnt)
+            for (int q = 0; q < M; ++q)
                 o[q] = u[q];
+        } else {
+#pragma unroll
+            for (int q = 0; q < M; ++q)
+                if (c0 + q >= 0 && c0 + q < cnt)
+                    o[q] = u[q];
+        }
     }
 }
 
@@ -469,6 +597,7 @@ struct WindowBatchArgs {
     const BatchTask* tasks;
     unsigned count;
     int stage;
+    int halo;
     unsigned long long guard;
 };
 
@@ -488,7 +617,7 @@ __global__ __launch_bounds__(64) void window_batch_kernel(WindowBatchArgs<S> b)
     g.n = I.n;
     g.own = I.own;
     g.steps = I.base + (b.stage < I.rem);
-    g.halo = g.steps * S::NPHASE;
+    g.halo = b.halo;
     g.c = I.c;
     g.fused = I.fused;
     if constexpr (is_ks<S>) {
@@ -499,6 +628,7 @@ __global__ __launch_bounds__(64) void window_batch_kernel(WindowBatchArgs<S> b)
         static_assert(sizeof(T) == 8, "the batch takes binary64 stencils");
         g.big = std::numeric_limits<T>::max() / (b.stage == 0 ? 16 : 8);
         g.tiny = I.e != 0 ? __hiloint2double((1 + I.e * g.steps) << 20, 0) : 0.0;   // 2^(e*steps - 1022)
+        g.rows = g.steps;
         g.guard = b.stage == 0 ? b.guard : 0;
     }
     window_tile<S, M>(g, (unsigned)task.tile);
@@ -518,7 +648,7 @@ __global__ __launch_bounds__(64) void window_batch_kernel(WindowBatchArgs<S> b)
 // step's field (8 bytes a point and step; the lane-frame stages kept 6) costs
 // no recomputation beyond v, no LDS and no halo for forward values: against
 // swept_adjoint_kernel's stages of 8 KS steps (forward recomputed, then
-// reversed, two rows a level) 2.2 -> 0.7 us a step at 2^16 points.
+// reversed, two rows a level) 2.2 -> 0.6 us a step at 2^16 points.
 template <class S>
 struct WindowAdjArgs {
     const typename S::T* u0;      // field of step 0
@@ -571,9 +701,27 @@ __global__ __launch_bounds__(64) void window_adjoint_kernel(WindowAdjArgs<S> g)
     const int cnt = (int)(left < g.own ? left : g.own);
     auto field = [&](int64_t j) { return j == 0 ? g.u0 : g.kept + (j - g.kept0) * g.n; };
     const int64_t last = g.first + g.steps;
+    // byte offsets of the lane's points in a field (n < 2^28: 32 bits): the
+    // loads of the loop then have no branch for windows across the seam, which
+    // would make each wait for its data at once
+    unsigned off[M];
+    {
+        int64_t x = (x0 + (int)threadIdx.x * M) % g.n;
+        x = x < 0 ? x + g.n : x;
+#pragma unroll
+        for (int q = 0; q < M; ++q) {
+            off[q] = (unsigned)x * (unsigned)sizeof(T);
+            x = x + 1 == g.n ? 0 : x + 1;
+        }
+    }
+    auto load = [&](T (&v)[M], const T* p) {
+#pragma unroll
+        for (int q = 0; q < M; ++q)
+            v[q] = *reinterpret_cast<const T*>(reinterpret_cast<const unsigned char*>(p) + off[q]);
+    };
     T lam[M], f[M];
     if (g.in != nullptr) {
-        window_load<T, M>(lam, g.in, g.n, x0);
+        load(lam, g.in);
     } else {
 #pragma unroll
         for (int q = 0; q < M; ++q)
@@ -581,7 +729,7 @@ __global__ __launch_bounds__(64) void window_adjoint_kernel(WindowAdjArgs<S> g)
     }
     Ad a[M];
     if (g.seed != 0 && last >= g.win_first) {
-        window_load<T, M>(f, field(last), g.n, x0);
+        load(f, field(last));
 #pragma unroll
         for (int q = 0; q < M; ++q)
             a[q] = S::seed(lam[q], g.two_w, f[q], true);
@@ -590,19 +738,11 @@ __global__ __launch_bounds__(64) void window_adjoint_kernel(WindowAdjArgs<S> g)
         for (int q = 0; q < M; ++q)
             a[q] = S::seed(lam[q], g.two_w, T(0), false);
     }
-    // a step's forward values: for KS every step's, for heat those of the
-    // window (its transposed step reads none)
-    constexpr bool kAlways = S::NPHASE != 1;
-    int64_t j = last - 1;
-    if (g.steps > 0 && (kAlways || j >= g.win_first))
-        window_load<T, M>(f, field(j), g.n, x0);
-    for (; j >= g.first; --j) {
-        T fn[M];   // the next step's field, on its way while this one is computed
-#pragma unroll
-        for (int q = 0; q < M; ++q)
-            fn[q] = T(0);
-        if (j > g.first && (kAlways || j - 1 >= g.win_first))
-            window_load<T, M>(fn, field(j - 1), g.n, x0);
+    // the step's field, and the next one's on its way while the step is computed
+    load(f, field(g.steps > 0 ? last - 1 : g.first));
+    for (int64_t j = last - 1; j >= g.first; --j) {
+        T fn[M];
+        load(fn, field(j > g.first ? j - 1 : j));
         Kept k[M];
 #pragma unroll
         for (int q = 0; q < M; ++q)
