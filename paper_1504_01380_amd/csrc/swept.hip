@@ -1828,7 +1828,11 @@ WindowForm<S> window_form(const typename S::Consts& c, int64_t L)
         f.fused = fma ? f.exact : moderate;
         f.ops = fma ? (f.exact ? 18 : 22) : (f.exact ? 21 : (f.fused ? 27 : 30));
     } else if constexpr (has_faces<S>::value) {
-        f.ops = 480;
+        auto moderate = [](double x, int e) {
+            return std::fabs(x) >= std::ldexp(1.0, -e) && std::fabs(x) <= std::ldexp(1.0, e);
+        };
+        f.fused = moderate(c.gm1, 10) && moderate(c.ch, 40) && moderate(c.cf, 40);
+        f.ops = f.fused ? 300 : 480;
     } else if constexpr (std::is_base_of_v<HeatFma<typename S::T>, S>) {
         f.ops = 3;
     } else if constexpr (has_fused_form<S>) {

@@ -152,6 +152,52 @@ def test_euler_bitwise(sw, oracle_mod, n, nsteps, smooth):
     assert same_bits(run(sw, q0, nsteps, "euler", par), oracle_mod.euler(q0, nsteps, *par))
 
 
+def euler_states(kind, n, seed):
+    """Fields on both sides of the ranges the fast Euler step needs."""
+    q = workloads.euler_smooth(n, seed=seed)
+    g = workloads.rng(seed)
+    at = slice(n // 3, n // 3 + n // 8)
+    if kind == "negative_zero":          # gas at rest with m = -0.0
+        q = workloads.euler_mirrored_sod(n)
+        q[:, 1] = -0.0
+    elif kind == "random":               # strong random jumps, many limiter branches
+        q = workloads.euler_state(g.uniform(0.1, 2.0, n), g.uniform(-1, 1, n), g.uniform(0.1, 2, n))
+    elif kind == "blast":
+        q = workloads.euler_state(1.0, 0.0, np.where(np.arange(n) % 97 < 9, 1e4, 1e-3))
+    elif kind == "tiny_momentum":        # below the range, subnormal, and zero
+        q[:, 1] = 0.0
+        q[at, 1] = 1e-200
+        q[at.start + 3, 1], q[at.start + 5, 1] = 5e-324, -1e-310
+    elif kind == "scaled_up":            # density and energy above it
+        q[:, :] *= 1e60
+    elif kind == "scaled_down":
+        q[:, :] *= 1e-70
+    elif kind == "near_vacuum":
+        q[at] = workloads.euler_state(1e-35, 0.3, 1e-36)
+    elif kind == "unphysical":           # negative pressure, then negative density
+        q[at, 2] = 0.01 * q[at, 2]
+        q[n // 2, 0] = -0.3
+    elif kind == "nan":
+        q[n // 2, 1] = np.nan
+    elif kind == "inf":
+        q[n // 2, 2] = np.inf
+    return np.ascontiguousarray(q)
+
+
+@pytest.mark.parametrize("kind", ["smooth", "negative_zero", "random", "blast", "tiny_momentum",
+                                  "scaled_up", "scaled_down", "near_vacuum", "unphysical", "nan",
+                                  "inf"])
+@pytest.mark.parametrize("n,nsteps", [(300, 24), (5000, 13)])
+def test_euler_ranges(sw, oracle_mod, kind, n, nsteps):
+    """The fast Euler step where its ranges hold, and windows that start outside
+    them or leave them during a stage: the oracle's bits (NaNs by place)."""
+    q0 = euler_states(kind, n, seed=n + nsteps)
+    par = [0.05 / n, 1.0 / n, workloads.EULER_GAMMA]
+    got = run(sw, q0, nsteps, "euler", par)
+    want = oracle_mod.euler(q0, nsteps, *par)
+    assert same_up_to_nan(got, want)
+
+
 @pytest.mark.parametrize("spread", [False, True])
 def test_batch_bitwise(sw, oracle_mod, spread):
     """Batches on windows: rings far smaller than a window and larger ones,
