@@ -154,10 +154,11 @@ def _prepare(u: torch.Tensor, sid: int) -> int:
             raise ValueError("Euler fields are contiguous (N, 3) tensors of (rho, m, E)")
     elif not u.is_contiguous() or u.dim() != 1:
         raise ValueError("u must be a contiguous 1-D tensor")
-    if _device != u.device.index:
-        init(u.device.index)
-    _check(_lib.swept_set_stream(ctypes.c_void_p(torch.cuda.current_stream(u.device).cuda_stream)),
-           "swept_set_stream")
+    index = u.device.index
+    if _device != index:
+        init(index)
+    # the handle alone: a Stream object beside it takes longer than the call below
+    _check(_lib.swept_set_stream(torch._C._cuda_getCurrentRawStream(index)), "swept_set_stream")
     return u.shape[0]
 
 

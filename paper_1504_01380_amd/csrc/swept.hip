@@ -1653,22 +1653,23 @@ struct WindowPlan {
     double cost = 1e300;   // predicted time, ns
 };
 
-// Time of one row (one time step of one window of 64*M points) of a wave
-// alone on its SIMD, fitted to sweeps of M and h on MI355X: heat (three
-// operations a point) 17 + 5.6 M ns over M = 2..20, KS (21) 35 + 41 M over
-// M = 2..20, Euler (490) 0.15 + 1.08 M us over M = 1..6.
+// Time of one row (one time step of one window of 64*M points), fitted to sweeps
+// of M and h on MI355X.  Alone on its SIMD: heat (three operations a point)
+// 17 + 5.6 M ns over M = 2..20, KS (21) 35 + 41 M over M = 2..20, Euler (300)
+// 0.12 + 0.54 M us over M = 1..6.
 struct WindowCost {
     double lat;      // ns a row takes beside its points
     double per;      // ns per point and lane
+    double many;     // part of `per` a row takes where a SIMD has several waves
 };
 
 WindowCost window_cost(int id, int ops)
 {
     switch (base_id(id)) {
-    case SWEPT_HEAT_F32: return WindowCost{17.0, 1.4 * ops};
-    case SWEPT_KS_F64: return WindowCost{35.0, 1.95 * ops};
-    case SWEPT_EULER_F64: return WindowCost{150.0, 2.2 * ops};
-    default: return WindowCost{17.0, 1.87 * ops};
+    case SWEPT_HEAT_F32: return WindowCost{17.0, 1.4 * ops, 0.88};
+    case SWEPT_KS_F64: return WindowCost{35.0, 1.95 * ops, 0.88};
+    case SWEPT_EULER_F64: return WindowCost{120.0, 1.8 * ops, 1.05};
+    default: return WindowCost{17.0, 1.87 * ops, 0.88};
     }
 }
 
@@ -1678,6 +1679,7 @@ size_t field_bytes(int id);
 constexpr int kWindowHeat[] = {2, 3, 4, 6, 8, 12, 18, 20, 24, 32, 48};
 constexpr int kWindowKs[] = {2, 3, 4, 5, 6, 8, 10, 12, 18, 20, 24};
 constexpr int kWindowEuler[] = {1, 2, 3, 4, 6};
+constexpr int kWindowSizes = 11;                 // the longest of these lists
 constexpr int kWindowAdj[] = {2, 3, 4, 6, 8};    // the adjoint, and stages that keep every step
 
 // What a plan is made for: the sizes built, points a step's dependence grows by
@@ -1695,6 +1697,7 @@ struct WindowShape {
 template <size_t N>
 WindowShape window_shape(const int (&sizes)[N], int id, int ops)
 {
+    static_assert(N <= kWindowSizes, "window_plan's table");
     return WindowShape{sizes, (int)N, substeps_of(id), 0, (double)field_bytes(id),
                        window_cost(id, ops), false};
 }
@@ -1713,53 +1716,84 @@ WindowShape window_shape(const int (&sizes)[N], int id, int ops)
 // and out (4.5 us in all at 2^20 binary64 points, where all waves move data at
 // the same time: 7 TB/s; half hidden by other waves' rows once a SIMD holds
 // several), and h rows; 1024 SIMDs share the tiles, and a row takes the longer
-// of a lone wave's time and the issue time of all the waves of a SIMD (a lone
-// wave issues at 0.88 of the rate of several).  Deep stages spread the launch,
-// wide windows the halo; few tiles (small grids) want small windows, whose
-// rows are short.
+// of a lone wave's time and the issue time of all the waves of a SIMD
+// (WindowCost::many).  Deep stages spread the launch, wide windows the halo;
+// few tiles (small grids) want small windows, whose rows are short.
+//
+// A call makes its plan anew, while the device waits on a short call, so most
+// pairs of size and depth are left at a bound of their time that takes two
+// divisions: 1.5 us instead of 2.9 at 1000 points and 100 steps, 2.7 instead of
+// 7.2 at 4096 points and 10000.  Depths go in 64ths of the window: in 32nds a
+// 384-cell Euler window had stages of 3 and 6 steps (13.1 and 14.2 us a step
+// at 2^20 cells) but none of 4 (12.2).
 [[maybe_unused]] WindowPlan window_plan(const WindowShape& shape, int64_t n, int64_t nsteps)
 {
+    struct Depth {
+        int M, h;
+        double bound;
+    };
+    constexpr int kDepths = 28;   // up to 28/64 of the window on either side
+    Depth depths[kWindowSizes * kDepths];
     const int R = shape.radius;
     const WindowCost c = shape.cost;
-    WindowPlan best;
+    const double steps = (double)nsteps, points = (double)n / 1024.0;
+    const double stage = 2200.0 + (double)n * shape.bytes / 7000.0;
+    const double hmax = (double)((nsteps + 1) / 2);
+    int count = 0, first = 0;
     for (int i = 0; i < shape.count; ++i) {
-        const int M = shape.sizes[i];
-        const int64_t W = 64 * M;
-        int64_t last = 0;
-        for (int f = 1; f <= 14; ++f) {
-            int64_t h = std::min(W * f / (32 * R), (nsteps + 1) / 2);
-            if (h < 1 || h == last)
+        const int M = shape.sizes[i], W = 64 * M;
+        const double row = c.lat + c.per * M, wave = c.many * c.per * M;
+        int last = 0;
+        for (int f = 1; f <= kDepths; ++f) {
+            const int h = (int)std::min((double)(W * f / (64 * R)), hmax);
+            if (h <= last)
                 continue;
             last = h;
-            WindowPlan p;
-            p.stages = (nsteps + h - 1) / h;
-            p.stages += p.stages & 1;
-            p.h = (nsteps + p.stages - 1) / p.stages;
-            // halos and owned parts are multiples of 8 and 16 points (whole lines;
-            // misaligned ones took 24.8 us a stage instead of 20 at 2^20 + 1
-            // points), or of the lanes' M points
-            const int64_t grain = shape.lanes ? M : 8, own_grain = shape.lanes ? M : 16;
-            p.halo = (int)((R * p.h + shape.extra + grain - 1) / grain * grain);
-            const int64_t room = (W - 2 * p.halo) / own_grain * own_grain;
-            if (room < own_grain)
-                continue;
-            p.M = M;
-            p.tiles = (n + room - 1) / room;
-            if (p.tiles > (int64_t(1) << 30))
-                continue;
-            p.own = (n + p.tiles - 1) / p.tiles;
-            p.own = (p.own + own_grain - 1) / own_grain * own_grain;
-            p.tiles = (n + p.own - 1) / p.own;
-            const double w = (double)p.tiles / 1024.0;
-            const double waves = w <= 8.0 ? std::ceil(w) : w + 0.5;
-            const double row = std::max(c.lat + c.per * M, waves * (5.0 + 0.88 * c.per * M));
-            const double mem = (double)n * shape.bytes * (1.0 + (double)W / (double)p.own) /
-                               (w > 2.0 ? 14000.0 : 7000.0);
-            p.cost = (double)p.stages * (2200.0 + mem + (double)p.h * row);
-            if (p.cost < best.cost)
-                best = p;
+            const double bound =
+                steps * (stage / h + std::max(row, points / (double)(W - 2 * R * h) * wave));
+            depths[count] = Depth{M, h, bound};
+            if (bound < depths[first].bound)
+                first = count;
+            ++count;
         }
     }
+    WindowPlan best;
+    auto look = [&](const Depth& d) {
+        const int M = d.M;
+        const int64_t W = 64 * M;
+        WindowPlan p;
+        p.stages = (nsteps + d.h - 1) / d.h;
+        p.stages += p.stages & 1;
+        p.h = (nsteps + p.stages - 1) / p.stages;
+        // halos and owned parts are multiples of 8 and 16 points (whole lines;
+        // misaligned ones took 24.8 us a stage instead of 20 at 2^20 + 1
+        // points), or of the lanes' M points
+        const int64_t grain = shape.lanes ? M : 8, own_grain = shape.lanes ? M : 16;
+        p.halo = (int)((R * p.h + shape.extra + grain - 1) / grain * grain);
+        const int64_t room = (W - 2 * p.halo) / own_grain * own_grain;
+        if (room < own_grain)
+            return;
+        p.M = M;
+        p.tiles = (n + room - 1) / room;
+        if (p.tiles > (int64_t(1) << 30))
+            return;
+        p.own = (n + p.tiles - 1) / p.tiles;
+        p.own = (p.own + own_grain - 1) / own_grain * own_grain;
+        p.tiles = (n + p.own - 1) / p.own;
+        const double w = (double)p.tiles / 1024.0;
+        const double waves = w <= 8.0 ? std::ceil(w) : w + 0.5;
+        const double row = std::max(c.lat + c.per * M, waves * (5.0 + c.many * c.per * M));
+        const double mem = (double)n * shape.bytes * (1.0 + (double)W / (double)p.own) /
+                           (w > 2.0 ? 14000.0 : 7000.0);
+        p.cost = (double)p.stages * (2200.0 + mem + (double)p.h * row);
+        if (p.cost < best.cost)
+            best = p;
+    };
+    if (count > 0)
+        look(depths[first]);
+    for (int i = 0; i < count; ++i)
+        if (depths[i].bound < best.cost)
+            look(depths[i]);
     return best;
 }
 
@@ -1832,7 +1866,7 @@ WindowForm<S> window_form(const typename S::Consts& c, int64_t L)
             return std::fabs(x) >= std::ldexp(1.0, -e) && std::fabs(x) <= std::ldexp(1.0, e);
         };
         f.fused = moderate(c.gm1, 10) && moderate(c.ch, 40) && moderate(c.cf, 40);
-        f.ops = f.fused ? 300 : 480;
+        f.ops = f.fused ? 300 : 580;
     } else if constexpr (std::is_base_of_v<HeatFma<typename S::T>, S>) {
         f.ops = 3;
     } else if constexpr (has_fused_form<S>) {
@@ -2137,7 +2171,7 @@ constexpr int kWindowBatchKs[] = {4, 8, 12, 18};
                 continue;
             const double stages = std::ceil((double)smax / (double)h);
             const double rows = (sns + (double)h * sn) / room + 0.5 * (ss + count * (double)h);
-            const double full = rows * (5.0 + 0.88 * c.per * M) / 1024.0 +
+            const double full = rows * (5.0 + c.many * c.per * M) / 1024.0 +
                                 stages * 0.5 * (double)h * c.per * M;
             const double alone = stages * (double)h * (c.lat + c.per * M);
             const double mem = 16.0 * (sns / (double)h + sn) / 5000.0;
