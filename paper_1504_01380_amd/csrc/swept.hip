@@ -2136,10 +2136,18 @@ int window_dispatch(void* u, int64_t nx, int64_t nsteps, int32_t id, const doubl
 }
 #endif
 
-// The batch on register windows: per stage one launch per stencil over the
-// tiles of the instances with stages to go.  All instances of a stencil share
-// the window size and the deepest stage; each spreads its own steps over an
-// even number of stages.
+// The batch on register windows: two chains of launches on two streams.  A chain
+// advances its KS instances and then its heat instances, per stage one launch
+// over the tiles of the instances with stages to go.  All instances of a stencil
+// share the window size and the deepest stage; each spreads its own steps over
+// an even number of stages.
+//
+// Two chains, because a launch ends with its last waves: 5352 KS tiles are 5.2
+// waves a SIMD and took the 63.5 us of six, and each launch's first loads and
+// last stores leave the SIMDs idle.  The other chain's waves run there: 512
+// instances of 256..65536 points and 100..2000 steps took 4.22 ms in one chain,
+// 3.45 in two (three or four chains: 3.5..3.9; the halves mixed instead of cut by
+// length: 3.7; different window sizes in the two: 3.4..4.1).
 struct WindowBatchPlan {
     int M = 0;
     int64_t h = 0;
@@ -2184,6 +2192,13 @@ constexpr int kWindowBatchKs[] = {4, 8, 12, 18};
         }
     }
     return best;
+}
+
+// points a tile owns at most
+template <class S>
+int64_t window_batch_room(const WindowBatchPlan& plan)
+{
+    return (64 * plan.M - 2 * ((S::NPHASE * plan.h + 7) / 8 * 8)) / 16 * 16;
 }
 
 // Host tables of a batch on their way to the device: two pinned buffers used in
@@ -2237,6 +2252,47 @@ Staging g_staging;
     return SWEPT_OK;
 }
 
+// A stream of the library's own for the second chain of a batch.  It starts
+// after what the caller's stream holds (side_fork), and the caller's stream
+// goes on after it (side_join), so that fields and scratch are used in the
+// order of the caller's stream.
+struct Side {
+    hipStream_t stream = nullptr;
+    hipEvent_t fork = nullptr, join = nullptr;
+};
+Side g_side;
+
+[[maybe_unused]] int side_fork(hipStream_t* out)
+{
+    Side& g = g_side;
+    if (!g.stream)
+        HIP_TRY(hipStreamCreateWithFlags(&g.stream, hipStreamNonBlocking));
+    for (hipEvent_t* e : {&g.fork, &g.join})
+        if (!*e)
+            HIP_TRY(hipEventCreateWithFlags(e, hipEventDisableTiming));
+    HIP_TRY(hipEventRecord(g.fork, g_ctx.stream));
+    HIP_TRY(hipStreamWaitEvent(g.stream, g.fork, 0));
+    *out = g.stream;
+    return SWEPT_OK;
+}
+
+[[maybe_unused]] int side_join()
+{
+    HIP_TRY(hipEventRecord(g_side.join, g_side.stream));
+    HIP_TRY(hipStreamWaitEvent(g_ctx.stream, g_side.join, 0));
+    return SWEPT_OK;
+}
+
+void side_release()
+{
+    for (hipEvent_t e : {g_side.fork, g_side.join})
+        if (e)
+            (void)hipEventDestroy(e);
+    if (g_side.stream)
+        (void)hipStreamDestroy(g_side.stream);
+    g_side = Side{};
+}
+
 void staging_release()
 {
     for (int i = 0; i < 2; ++i) {
@@ -2267,59 +2323,78 @@ int run_window_batch(void* const*, const int64_t*, const int64_t*, const int32_t
     return fail(SWEPT_EUNSUPPORTED, "the counting build has no window schedule");
 }
 #else
-// one stencil of a batch: its instances, tasks and launches
+// an instance of a batch that has steps to make
+template <class S>
+struct WindowJob {
+    int64_t j;          // its place in the call
+    int64_t n, steps;
+    WindowForm<S> form;
+    typename S::Consts c;
+};
+
+// the plan of all instances of a stencil; tiles: of a first stage, ops: a point's operations
+template <class S>
+WindowBatchPlan window_batch_plan(int id, const std::vector<WindowJob<S>>& jobs, int64_t* tiles,
+                                  int* ops)
+{
+    if (jobs.empty())
+        return WindowBatchPlan{};
+    double sn = 0, ss = 0, sns = 0;
+    int64_t smax = 0, hmax = int64_t(1) << 40;
+    for (const WindowJob<S>& job : jobs) {
+        sn += (double)job.n;
+        ss += (double)job.steps;
+        sns += (double)job.n * (double)job.steps;
+        smax = std::max(smax, job.steps);
+        *ops = std::max(*ops, job.form.ops);
+        if (job.form.rows > 0)   // one look at the smallest value a stage
+            hmax = std::min<int64_t>(hmax, job.form.rows);
+    }
+    const WindowBatchPlan plan =
+        window_batch_plan(id, *ops, hmax, sn, ss, sns, (double)jobs.size(), smax);
+    const int64_t room = window_batch_room<S>(plan);
+    for (const WindowJob<S>& job : jobs)
+        *tiles += (job.n + room - 1) / room;
+    return plan;
+}
+
+// one stencil's part of a chain: its instances, tasks and launches
 template <class S>
 struct WindowBatch {
+    std::vector<WindowJob<S>> jobs;
     std::vector<WindowInst<S>> inst;
     std::vector<int64_t> stages;       // per instance
     std::vector<BatchTask> tasks;
     std::vector<int64_t> live;         // live[s]: tasks of stage s
     WindowBatchPlan plan;
+    WindowBatchArgs<S> args{};
 
-    // instances j of ids[j] == id, in the order given
-    void build(int id, const std::vector<int64_t>& js, void* const* u, const int64_t* nx,
-               const int64_t* nsteps, const std::vector<WindowForm<S>>& forms,
-               const std::vector<typename S::Consts>& consts)
+    void build(void* const* u)
     {
-        if (js.empty())
+        if (jobs.empty())
             return;
-        double sn = 0, ss = 0, sns = 0;
-        int64_t smax = 0, hmax = int64_t(1) << 40;
-        int ops = 0;
-        for (size_t q = 0; q < js.size(); ++q) {
-            const int64_t j = js[q];
-            sn += (double)nx[j];
-            ss += (double)nsteps[j];
-            sns += (double)nx[j] * (double)nsteps[j];
-            smax = std::max(smax, nsteps[j]);
-            ops = std::max(ops, forms[q].ops);
-            if (forms[q].rows > 0)   // one look at the smallest value a stage
-                hmax = std::min<int64_t>(hmax, forms[q].rows);
-        }
-        plan = window_batch_plan(id, ops, hmax, sn, ss, sns, (double)js.size(), smax);
-        const int64_t halo = (S::NPHASE * plan.h + 7) / 8 * 8;
-        const int64_t room = (64 * plan.M - 2 * halo) / 16 * 16;
-        args.halo = (int)halo;
-        inst.resize(js.size());
-        stages.resize(js.size());
-        std::vector<int64_t> tiles(js.size());
-        std::vector<int> order(js.size());
-        for (size_t q = 0; q < js.size(); ++q) {
-            const int64_t j = js[q];
+        const int64_t room = window_batch_room<S>(plan);
+        args.halo = (int)((S::NPHASE * plan.h + 7) / 8 * 8);
+        inst.resize(jobs.size());
+        stages.resize(jobs.size());
+        std::vector<int64_t> tiles(jobs.size());
+        std::vector<int> order(jobs.size());
+        for (size_t q = 0; q < jobs.size(); ++q) {
+            const WindowJob<S>& job = jobs[q];
             WindowInst<S>& I = inst[q];
-            int64_t st = (nsteps[j] + plan.h - 1) / plan.h;
+            int64_t st = (job.steps + plan.h - 1) / plan.h;
             st += st & 1;
-            const int64_t t = (nx[j] + room - 1) / room;
-            I.u = static_cast<typename S::T*>(u[j]);
-            I.n = nx[j];
-            I.own = (int)(((nx[j] + t - 1) / t + 15) / 16 * 16);
-            I.base = (int)(nsteps[j] / st);
-            I.rem = (int)(nsteps[j] % st);
-            I.fused = forms[q].fused;
-            I.e = is_ks<S> ? (int)forms[q].exact : forms[q].e;
-            I.c = consts[q];
+            const int64_t t = (job.n + room - 1) / room;
+            I.u = static_cast<typename S::T*>(u[job.j]);
+            I.n = job.n;
+            I.own = (int)(((job.n + t - 1) / t + 15) / 16 * 16);
+            I.base = (int)(job.steps / st);
+            I.rem = (int)(job.steps % st);
+            I.fused = job.form.fused;
+            I.e = is_ks<S> ? (int)job.form.exact : job.form.e;
+            I.c = job.c;
             stages[q] = st;
-            tiles[q] = (nx[j] + I.own - 1) / I.own;
+            tiles[q] = (job.n + I.own - 1) / I.own;
             order[q] = (int)q;
         }
         std::stable_sort(order.begin(), order.end(),
@@ -2351,20 +2426,34 @@ struct WindowBatch {
         args.tasks = reinterpret_cast<const BatchTask*>(dev + at);
     }
 
-    WindowBatchArgs<S> args{};
-
     template <int... MS>
-    void launch(int64_t s, std::integer_sequence<int, MS...>)
+    void launch(size_t s, hipStream_t st, std::integer_sequence<int, MS...>)
     {
         args.stage = (int)s;
-        args.count = (unsigned)live[(size_t)s];
+        args.count = (unsigned)live[s];
         const dim3 grid((args.count + 7) / 8 * 8), block(64);
         auto one = [&](auto m) {
             constexpr int MM = decltype(m)::value;
             if (plan.M == MM)
-                hipLaunchKernelGGL((window_batch_kernel<S, MM>), grid, block, 0, g_ctx.stream, args);
+                hipLaunchKernelGGL((window_batch_kernel<S, MM>), grid, block, 0, st, args);
         };
         (one(std::integral_constant<int, MS>{}), ...);
+    }
+};
+
+// one chain of launches
+struct WindowChain {
+    WindowBatch<KSF64> ks;
+    WindowBatch<HeatF64> heat;
+
+    bool empty() const { return ks.jobs.empty() && heat.jobs.empty(); }
+    size_t length() const { return ks.live.size() + heat.live.size(); }
+    void launch(size_t s, hipStream_t st)
+    {
+        if (s < ks.live.size())
+            ks.launch(s, st, std::integer_sequence<int, 4, 8, 12, 18>{});
+        else if (s < length())
+            heat.launch(s - ks.live.size(), st, std::integer_sequence<int, 4, 8, 16, 32>{});
     }
 };
 
@@ -2376,11 +2465,8 @@ int run_window_batch(void* const* u, const int64_t* nx, const int64_t* nsteps, c
     HIP_TRY(hipStreamIsCapturing(g_ctx.stream, &cap));
     if (cap != hipStreamCaptureStatusNone)
         return fail(SWEPT_EHIP, "swept_advance_batch cannot be captured into a graph");
-    std::vector<int64_t> jh, jk;
-    std::vector<WindowForm<HeatF64>> fh;
-    std::vector<WindowForm<KSF64>> fk;
-    std::vector<HeatF64::Consts> ch;
-    std::vector<KSF64::Consts> ck;
+    std::vector<WindowJob<HeatF64>> heat;
+    std::vector<WindowJob<KSF64>> ks;
     bool any_heat = false, fusable = true;
     for (int64_t j = 0; j < count; ++j) {
         const int64_t L = nsteps[j] * substeps_of(ids[j]);
@@ -2389,58 +2475,93 @@ int run_window_batch(void* const* u, const int64_t* nx, const int64_t* nsteps, c
             const WindowForm<HeatF64> f = window_form<HeatF64>(c, L);
             any_heat = true;
             fusable = fusable && f.fused;
-            if (L > 0) {
-                jh.push_back(j);
-                fh.push_back(f);
-                ch.push_back(c);
-            }
+            if (L > 0)
+                heat.push_back({j, nx[j], nsteps[j], f, c});
         } else if (L > 0) {
             const KSF64::Consts c = ks_consts(params + 2 * j);
-            jk.push_back(j);
-            fk.push_back(window_form<KSF64>(c, L));
-            ck.push_back(c);
+            ks.push_back({j, nx[j], nsteps[j], window_form<KSF64>(c, L), c});
         }
     }
     // one decision on the fused heat forms for the whole batch
     if (!fusable)
-        for (auto& f : fh)
-            f = WindowForm<HeatF64>{};
-    WindowBatch<HeatF64> h;
-    WindowBatch<KSF64> k;
-    h.build(SWEPT_HEAT_F64, jh, u, nx, nsteps, fh, ch);
-    k.build(SWEPT_KS_F64, jk, u, nx, nsteps, fk, ck);
-    if (h.tasks.size() >= (size_t(1) << 30) || k.tasks.size() >= (size_t(1) << 30))
-        return fail(SWEPT_EUNSUPPORTED, "swept_advance_batch: too many tiles");
+        for (auto& job : heat)
+            job.form = WindowForm<HeatF64>{};
+
+    // The chains.  Up to a wave a SIMD what counts is the number of launches one
+    // after another: KS in one chain, heat in the other.  Beyond that each chain
+    // gets half of the work, in the order KS by falling steps, heat by falling
+    // steps: the first chain keeps its launches full to the end, and the heat
+    // instances fill the second one's once its shorter KS runs are over.
+    WindowChain chain[2];
+    int64_t tiles = 0;
+    int ops_ks = 0, ops_heat = 0;
+    chain[0].ks.plan = chain[1].ks.plan = window_batch_plan(SWEPT_KS_F64, ks, &tiles, &ops_ks);
+    chain[0].heat.plan = chain[1].heat.plan =
+        window_batch_plan(SWEPT_HEAT_F64, heat, &tiles, &ops_heat);
+    if (tiles <= 1024) {
+        chain[0].ks.jobs = std::move(ks);
+        chain[1].heat.jobs = std::move(heat);
+    } else {
+        auto longer = [](const auto& a, const auto& b) { return a.steps > b.steps; };
+        std::stable_sort(ks.begin(), ks.end(), longer);
+        std::stable_sort(heat.begin(), heat.end(), longer);
+        auto work = [](const auto& job, int ops) { return (double)job.n * (double)job.steps * ops; };
+        double all = 0, done = 0;
+        for (const auto& job : ks)
+            all += work(job, ops_ks);
+        for (const auto& job : heat)
+            all += work(job, ops_heat);
+        for (const auto& job : ks) {
+            chain[2 * done >= all].ks.jobs.push_back(job);
+            done += work(job, ops_ks);
+        }
+        for (const auto& job : heat) {
+            chain[2 * done >= all].heat.jobs.push_back(job);
+            done += work(job, ops_heat);
+        }
+    }
+    if (chain[0].empty())
+        std::swap(chain[0], chain[1]);
 
     // scratch: the tables, then the spare fields
-    const size_t bh = h.table_bytes(), bk = k.table_bytes();
+    size_t tables = 0, spare = 0;
     auto al = [](int64_t n) { return ((size_t)n * sizeof(double) + 255) / 256 * 256; };
-    size_t spare = 0;
-    for (int64_t j : jh)
-        spare += al(nx[j]);
-    for (int64_t j : jk)
-        spare += al(nx[j]);
-    if (bh + bk > 0) {
-        int rc = ensure_scratch(bh + bk + spare);
+    auto each = [&](auto&& f) {
+        for (WindowChain& c : chain) {
+            f(c.ks);
+            f(c.heat);
+        }
+    };
+    bool fits = true;
+    each([&](auto& part) {
+        part.build(u);
+        fits = fits && part.tasks.size() < (size_t(1) << 30);
+        tables += part.table_bytes();
+        for (const auto& job : part.jobs)
+            spare += al(job.n);
+    });
+    if (!fits)
+        return fail(SWEPT_EUNSUPPORTED, "swept_advance_batch: too many tiles");
+    if (tables > 0) {
+        int rc = ensure_scratch(tables + spare);
         if (rc)
             return rc;
         unsigned char* dev = static_cast<unsigned char*>(g_ctx.scratch);
-        unsigned char* field = dev + bh + bk;
-        for (size_t q = 0; q < jh.size(); ++q) {
-            h.inst[q].spare = reinterpret_cast<double*>(field);
-            field += al(nx[jh[q]]);
-        }
-        for (size_t q = 0; q < jk.size(); ++q) {
-            k.inst[q].spare = reinterpret_cast<double*>(field);
-            field += al(nx[jk[q]]);
-        }
+        unsigned char* field = dev + tables;
         unsigned char* host = nullptr;
-        rc = staging_get(bh + bk, &host);
+        rc = staging_get(tables, &host);
         if (rc)
             return rc;
-        h.lay_out(host, dev);
-        k.lay_out(host + bh, dev + bh);
-        rc = staging_put(dev, bh + bk);
+        size_t at = 0;
+        each([&](auto& part) {
+            for (size_t q = 0; q < part.jobs.size(); ++q) {
+                part.inst[q].spare = reinterpret_cast<double*>(field);
+                field += al(part.jobs[q].n);
+            }
+            part.lay_out(host + at, dev + at);
+            at += part.table_bytes();
+        });
+        rc = staging_put(dev, tables);
         if (rc)
             return rc;
     }
@@ -2448,15 +2569,26 @@ int run_window_batch(void* const* u, const int64_t* nx, const int64_t* nsteps, c
         g_ctx.last_batch = false;
         g_ctx.last_form = fusable ? SWEPT_FORM_FUSED : SWEPT_FORM_CANONICAL;
         g_ctx.last_guard = fusable ? ++g_call_id : 0;
-        h.args.guard = g_ctx.last_guard;
+        chain[0].heat.args.guard = chain[1].heat.args.guard = g_ctx.last_guard;
     }
-    for (size_t s = 0; s < std::max(h.live.size(), k.live.size()); ++s) {
-        if (s < k.live.size())
-            k.launch((int64_t)s, std::integer_sequence<int, 4, 8, 12, 18>{});
-        if (s < h.live.size())
-            h.launch((int64_t)s, std::integer_sequence<int, 4, 8, 16, 32>{});
+    const bool two = !chain[1].empty();
+    hipStream_t second = g_ctx.stream;
+    if (two) {
+        int rc = side_fork(&second);
+        if (rc)
+            return rc;
     }
-    HIP_TRY(hipGetLastError());
+    for (size_t s = 0; s < std::max(chain[0].length(), chain[1].length()); ++s) {
+        chain[0].launch(s, g_ctx.stream);
+        chain[1].launch(s, second);
+    }
+    const hipError_t e = hipGetLastError();
+    if (two) {
+        int rc = side_join();
+        if (rc)
+            return rc;
+    }
+    HIP_TRY(e);
     return SWEPT_OK;
 }
 #endif
@@ -3598,6 +3730,7 @@ void swept_finalize(void)
     release_events();
     batch_release();
     staging_release();
+    side_release();
     swept_clear_tuning();
     g_batch_sched = SWEPT_BATCH_PERSISTENT;
     g_spin_limit = 0;

@@ -225,6 +225,37 @@ def test_batch_bitwise(sw, oracle_mod, spread):
         assert same_bits(u.cpu().numpy(), want), (st, n, steps, par)
 
 
+@pytest.mark.parametrize("heat,ks", [
+    ([(700001, 40), (300, 90), (200000, 7)], []),
+    ([], [(400002, 20), (64, 50), (300000, 1)]),
+    ([(500000, 30), (5, 3)], [(300001, 31), (4, 60)]),
+    ([(900000, 25), (300000, 60)], [(100, 9)]),
+    ([(4096, 100)], [(4096, 30)]),
+])
+@pytest.mark.parametrize("stream", [False, True])
+def test_batch_chains(sw, heat, ks, stream):
+    """The batch's two chains of launches: one stencil alone, KS and heat cut in
+    halves at different places, and a batch of few tiles.  What the caller's
+    stream does just before and after is ordered with both chains."""
+    import torch
+    insts = [("heat", n, k, [0.25]) for n, k in heat] + [("ks", n, k, KS_P) for n, k in ks]
+    u0 = [torch.from_numpy(workloads.white_noise(n, seed=n)).cuda() for _, n, _, _ in insts]
+    us = [torch.zeros_like(u) for u in u0]
+    want = [sw.advance(u.clone(), k, st, p) for u, (st, n, k, p) in zip(u0, insts)]
+    torch.cuda.synchronize()
+    with torch.cuda.stream(torch.cuda.Stream() if stream else torch.cuda.current_stream()):
+        for rep in range(3):
+            for u, a in zip(us, u0):
+                u.copy_(a)
+            sw.advance_batch(us, [i[2] for i in insts], [i[0] for i in insts], [i[3] for i in insts])
+            got = [u.clone() for u in us]
+            for u in us:
+                u.zero_()
+    torch.cuda.synchronize()
+    for g, w, i in zip(got, want, insts):
+        assert same_bits(g.cpu().numpy(), w.cpu().numpy()), i
+
+
 def test_batch_of_nothing(sw):
     import torch
     us = [torch.ones(10, dtype=torch.float64, device="cuda") for _ in range(3)]
