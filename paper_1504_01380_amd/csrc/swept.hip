@@ -2095,6 +2095,8 @@ int run_window_adjoint(const typename S::T* u0, typename S::T* grad, int64_t nx,
         a.win_first = win_first;
         a.two_w = (T)(2.0 * wgt);
         a.c = c;
+        if constexpr (ks)   // ks_adj_quick's conditions on the constants
+            a.quick = form.exact && c.c1 >= 1.0 && std::fabs(a.two_w) <= 1e60;
         int64_t done = 0;
         for (int64_t s = 0; s < p.stages; ++s) {
             const int64_t upto = stage_start(total, p.stages, s + 1);

@@ -811,12 +811,26 @@ __global__ __launch_bounds__(64) void window_batch_kernel(WindowBatchArgs<S> b)
 // recomputed v by three columns whatever the depth, which its first step
 // passes on: the halo is radius x steps, plus two for KS.
 //
-// What bounds it: the chain of a step, about 60 operations a point with 28
-// DPP moves, one wave per SIMD on the grids this is used for.  Keeping every
-// step's field (8 bytes a point and step; the lane-frame stages kept 6) costs
-// no recomputation beyond v, no LDS and no halo for forward values: against
-// swept_adjoint_kernel's stages of 8 KS steps (forward recomputed, then
-// reversed, two rows a level) 2.2 -> 0.6 us a step at 2^16 points.
+// What bounds it: the chain of a step, 40 operations a point (as written 54)
+// with 28 DPP moves, one wave per SIMD on the grids this is used for.  Keeping
+// every step's field (8 bytes a point and step; the lane-frame stages kept 6)
+// costs no recomputation beyond v, no LDS and no halo for forward values:
+// against swept_adjoint_kernel's stages of 8 KS steps (forward recomputed, then
+// reversed, two rows a level) 2.2 -> 0.86 us a step at 2^16 points, with the
+// operations as written and the next step's field loaded during a step.  That
+// load is from HBM and takes longer than the step: with the shorter form below
+// alone it stayed at 0.86, with the fields of four steps on their way as well
+// 0.69.
+//
+// KS with powers of two for c1 and c2 (ks_adj_quick): the same bits from fewer
+// operations.  2m, c2*x and c1*x are exact, so (l + r) - 2m = fma(-2, m, l + r),
+// a + c2*x = fma(c2, x, a) and c1*x - b = fma(c1, x, -b): each rounds once where
+// the written form does.  Nothing can underflow for c1, c2 >= 1 (a power of
+// two scales up); nothing overflows if the cotangents are at most 1e60 at
+// either end of each step, the source's weight is, and u is in kKsExact's range
+// (|v| <= 3e80, and by the bounds on the constants no value passes 1e200).
+// u's range also lets kKsExact recompute v.  Checked at every step like
+// ks_rows's; a window that leaves the range runs the stage again as written.
 template <class S>
 struct WindowAdjArgs {
     const typename S::T* u0;      // field of step 0
@@ -830,6 +844,7 @@ struct WindowAdjArgs {
     int64_t first;                // time step of `out`
     int64_t win_first;            // first time step of the objective's window
     typename S::T two_w;          // 2 * objective weight
+    int quick;                    // KS: the constants allow ks_adj_quick
     typename S::Consts c;
 };
 
@@ -854,12 +869,194 @@ __device__ __forceinline__ void adj_phase(typename S::Ad (&a)[M], const typename
     }
 }
 
-template <class S, int M>
-__global__ __launch_bounds__(64) void window_adjoint_kernel(WindowAdjArgs<S> g)
+// The four transposed KS sub-timesteps of all points: a, the cotangents of u'
+// in, of u out; u and v: the step's field and its middle level (KSF64::adj has
+// the operations as written).
+template <int M>
+__device__ __forceinline__ void ks_adj_quick(double (&a)[M], const double (&u)[M],
+                                             const double (&v)[M], const KSF64::Consts& k)
+{
+    // z[q]: the value of point q, from -1 (lane before) to M (lane after)
+    struct Row {
+        double l, r;
+        const double (&z)[M];
+        __device__ __forceinline__ explicit Row(const double (&x)[M])
+            : l(dpp_record<kWaveShr1>(x[M - 1])), r(dpp_record<kWaveShl1>(x[0])), z(x)
+        {
+        }
+        __device__ __forceinline__ double at(int q) const { return q < 0 ? l : q < M ? z[q] : r; }
+        __device__ __forceinline__ double lap(int q) const
+        {
+            return fmad(-2.0, z[q], at(q - 1) + at(q + 1));
+        }
+    };
+    // c1*(g[i+1]*f[i+1] - g[i-1]*f[i-1]) - g*((f[i+1] - f[i-1])*c1)
+    auto cross = [&](const Row& g, const Row& f, int q) {
+        const double d = (f.at(q + 1) - f.at(q - 1)) * k.c1;
+        return fmad(k.c1, g.at(q + 1) * f.at(q + 1) - g.at(q - 1) * f.at(q - 1), -(g.z[q] * d));
+    };
+    double g[M], x[M], y[M];
+#pragma unroll
+    for (int q = 0; q < M; ++q)
+        g[q] = k.dt * a[q];
+    {
+        const Row gr(g), vr(v);
+#pragma unroll
+        for (int q = 0; q < M; ++q) {
+            x[q] = cross(gr, vr, q);
+            y[q] = -fmad(k.c2, gr.lap(q), g[q]);
+        }
+    }
+    {
+        const Row yr(y);
+#pragma unroll
+        for (int q = 0; q < M; ++q) {
+            x[q] = fmad(k.c2, yr.lap(q), x[q]);
+            g[q] = k.h * x[q];
+        }
+    }
+    {
+        const Row gr(g), ur(u);
+#pragma unroll
+        for (int q = 0; q < M; ++q) {
+            a[q] = (a[q] + x[q]) + cross(gr, ur, q);
+            y[q] = -fmad(k.c2, gr.lap(q), g[q]);
+        }
+    }
+    {
+        const Row yr(y);
+#pragma unroll
+        for (int q = 0; q < M; ++q)
+            a[q] = fmad(k.c2, yr.lap(q), a[q]);
+    }
+}
+
+// The steps of a stage; lam: the cotangents of step `first`.  load(x, p): the
+// window of the field p; field(j): the kept field of step j.  False: a value
+// left the range of ks_adj_quick.
+template <class S, int M, bool kQuick, class Load, class Field>
+__device__ __forceinline__ bool adjoint_stage(typename S::T (&lam)[M], const WindowAdjArgs<S>& g,
+                                              Load&& load, Field&& field)
 {
     using T = typename S::T;
     using Ad = typename S::Ad;
     using Kept = typename S::Kept;
+    const int64_t last = g.first + g.steps;
+    // fields on their way while a step is computed
+    constexpr int kSlots = 4;
+    T f[kSlots][M];
+    if (g.in != nullptr) {
+        load(lam, g.in);
+    } else {
+#pragma unroll
+        for (int q = 0; q < M; ++q)
+            lam[q] = T(0);
+    }
+    Ad a[M];
+    if (g.seed != 0 && last >= g.win_first) {
+        load(f[0], field(last));
+#pragma unroll
+        for (int q = 0; q < M; ++q)
+            a[q] = S::seed(lam[q], g.two_w, f[0][q], true);
+    } else {
+#pragma unroll
+        for (int q = 0; q < M; ++q)
+            a[q] = S::seed(lam[q], g.two_w, T(0), false);
+    }
+    if constexpr (kQuick) {
+        bool in = true;
+#pragma unroll
+        for (int q = 0; q < M; ++q) {
+            lam[q] = S::grad(a[q]);
+            in = in && !(__builtin_fabs(lam[q]) > 1e60);   // (a NaN passes as itself)
+        }
+        if (!__all(in))
+            return false;
+    }
+    float big_a = 0.0f, tiny_u = __int_as_float(0x7f7fffff);
+    bool big_u = false;
+    auto step = [&](const T (&u)[M], bool source) {
+        if constexpr (kQuick) {
+            double v[M];
+            ks_half<S, kKsExact, M>(u, u, v, g.c.h * g.c.c2, g.c, g.c.c1 / g.c.c2);
+            ks_adj_quick<M>(lam, u, v, g.c);
+            if (source) {
+#pragma unroll
+                for (int q = 0; q < M; ++q)
+                    lam[q] = lam[q] + g.two_w * u[q];
+            }
+#pragma unroll
+            for (int q = 0; q < M; q += 2) {
+                const int q1 = q + 1 < M ? q + 1 : q;
+                const int x = __double2hiint(lam[q]), y = __double2hiint(lam[q1]);
+                const int z = __double2hiint(u[q]), w = __double2hiint(u[q1]);
+                asm("v_max3_f32 %0, %0, |%1|, |%2|" : "+v"(big_a) : "v"(x), "v"(y));
+                // (u is loaded anew at each step: its high word may be any)
+                big_u = big_u || __builtin_fabs(u[q]) > 1e30 || __builtin_fabs(u[q1]) > 1e30;
+                asm("v_min3_f32 %0, %0, |%1|, |%2|" : "+v"(tiny_u) : "v"(z), "v"(w));
+            }
+        } else {
+            Kept k[M];
+#pragma unroll
+            for (int q = 0; q < M; ++q)
+                k[q] = u[q];
+            if constexpr (S::NPHASE == 4) {
+                typename S::Pt P[M];
+#pragma unroll
+                for (int q = 0; q < M; ++q)
+                    P[q] = S::from_field(u[q]);
+                window_phase<S, 0, M>(P, g.c);
+                window_phase<S, 1, M>(P, g.c);
+                Kept kv[M];
+#pragma unroll
+                for (int q = 0; q < M; ++q)
+                    kv[q] = S::template keep<3>(P[q]);
+                adj_phase<S, 3, M>(a, kv, g.c);
+                adj_phase<S, 2, M>(a, kv, g.c);
+                adj_phase<S, 1, M>(a, k, g.c);
+            }
+            adj_phase<S, 0, M>(a, k, g.c);
+            if (source) {
+#pragma unroll
+                for (int q = 0; q < M; ++q)
+                    a[q] = S::source(a[q], k[q], g.two_w);
+            }
+        }
+    };
+    // (a field below the stage's steps is not read: the loads stop at `first`)
+    auto fetch = [&](T (&u)[M], int64_t j) { load(u, field(j > g.first ? j : g.first)); };
+#pragma unroll
+    for (int i = 0; i < kSlots; ++i)
+        fetch(f[i], last - 1 - i);
+    int64_t j = last - 1;
+    for (; j - (kSlots - 1) >= g.first; j -= kSlots) {
+#pragma unroll
+        for (int i = 0; i < kSlots; ++i) {
+            step(f[i], j - i >= g.win_first);
+            fetch(f[i], j - i - kSlots);
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < kSlots - 1; ++i)
+        if (j - i >= g.first)
+            step(f[i], j - i >= g.win_first);
+    if constexpr (kQuick) {
+        // high words: 1e60 = 0x4c63e9e4..., 2^-400 as in ks_rows
+        const bool in = big_a < __int_as_float(0x4c63e9e4) && !big_u &&
+                        tiny_u > __int_as_float(0x26f00000);
+        return (bool)__all(in);
+    } else {
+#pragma unroll
+        for (int q = 0; q < M; ++q)
+            lam[q] = S::grad(a[q]);
+        return true;
+    }
+}
+
+template <class S, int M>
+__global__ __launch_bounds__(64) void window_adjoint_kernel(WindowAdjArgs<S> g)
+{
+    using T = typename S::T;
     const unsigned tile = xcd_run(blockIdx.x, (unsigned)g.tiles);
     if (tile >= (unsigned)g.tiles)
         return;
@@ -868,7 +1065,6 @@ __global__ __launch_bounds__(64) void window_adjoint_kernel(WindowAdjArgs<S> g)
     const int64_t left = g.n - t0;
     const int cnt = (int)(left < g.own ? left : g.own);
     auto field = [&](int64_t j) { return j == 0 ? g.u0 : g.kept + (j - g.kept0) * g.n; };
-    const int64_t last = g.first + g.steps;
     // byte offsets of the lane's points in a field (n < 2^28: 32 bits): the
     // loads of the loop then have no branch for windows across the seam, which
     // would make each wait for its data at once
@@ -887,62 +1083,12 @@ __global__ __launch_bounds__(64) void window_adjoint_kernel(WindowAdjArgs<S> g)
         for (int q = 0; q < M; ++q)
             v[q] = *reinterpret_cast<const T*>(reinterpret_cast<const unsigned char*>(p) + off[q]);
     };
-    T lam[M], f[M];
-    if (g.in != nullptr) {
-        load(lam, g.in);
-    } else {
-#pragma unroll
-        for (int q = 0; q < M; ++q)
-            lam[q] = T(0);
-    }
-    Ad a[M];
-    if (g.seed != 0 && last >= g.win_first) {
-        load(f, field(last));
-#pragma unroll
-        for (int q = 0; q < M; ++q)
-            a[q] = S::seed(lam[q], g.two_w, f[q], true);
-    } else {
-#pragma unroll
-        for (int q = 0; q < M; ++q)
-            a[q] = S::seed(lam[q], g.two_w, T(0), false);
-    }
-    // the step's field, and the next one's on its way while the step is computed
-    load(f, field(g.steps > 0 ? last - 1 : g.first));
-    for (int64_t j = last - 1; j >= g.first; --j) {
-        T fn[M];
-        load(fn, field(j > g.first ? j - 1 : j));
-        Kept k[M];
-#pragma unroll
-        for (int q = 0; q < M; ++q)
-            k[q] = f[q];
-        if constexpr (S::NPHASE == 4) {
-            typename S::Pt P[M];
-#pragma unroll
-            for (int q = 0; q < M; ++q)
-                P[q] = S::from_field(f[q]);
-            window_phase<S, 0, M>(P, g.c);
-            window_phase<S, 1, M>(P, g.c);
-            Kept kv[M];
-#pragma unroll
-            for (int q = 0; q < M; ++q)
-                kv[q] = S::template keep<3>(P[q]);
-            adj_phase<S, 3, M>(a, kv, g.c);
-            adj_phase<S, 2, M>(a, kv, g.c);
-            adj_phase<S, 1, M>(a, k, g.c);
-        }
-        adj_phase<S, 0, M>(a, k, g.c);
-        if (j >= g.win_first) {
-#pragma unroll
-            for (int q = 0; q < M; ++q)
-                a[q] = S::source(a[q], k[q], g.two_w);
-        }
-#pragma unroll
-        for (int q = 0; q < M; ++q)
-            f[q] = fn[q];
-    }
-#pragma unroll
-    for (int q = 0; q < M; ++q)
-        lam[q] = S::grad(a[q]);
+    T lam[M];
+    bool done = false;
+    if constexpr (is_ks<S>)
+        done = g.quick != 0 && adjoint_stage<S, M, true>(lam, g, load, field);
+    if (!done)
+        adjoint_stage<S, M, false>(lam, g, load, field);
     window_store<T, M>(lam, g.out, t0, g.halo, cnt);
 }
 

@@ -286,6 +286,48 @@ def test_adjoint_bitwise(sw, oracle_mod, stencil, n, nsteps, first, with_cot):
     assert same_bits(g.cpu().numpy(), oracle(u0, nsteps, *par, first, 0.01, cot))
 
 
+@pytest.mark.parametrize("field,cot,weight", [
+    ("noise", "noise", 0.01), ("noise", "spikes", 0.0), ("noise", "subnormal", 0.0),
+    ("noise", "huge", 0.01), ("noise", "mixed", 0.01), ("noise", "noise", 1e300),
+    ("zeros", "noise", 0.01), ("tiny", "noise", 0.01), ("large", "noise", 0.01),
+    ("noise", "nan", 0.01),
+])
+@pytest.mark.parametrize("dx", [0.25, 0.5, 1.0, 0.7])
+def test_ks_adjoint_forms(sw, oracle_mod, field, cot, weight, dx):
+    """The adjoint's shorter form (c1 and c2 powers of two, c1 >= 1: dx = 1/4
+    and 1/2) and the operations as written, over fields and cotangents inside
+    and outside of its range: zeros, subnormals, 1e250 and NaN in some or all
+    windows."""
+    import torch
+    n, nsteps = 4098, 33
+    dt = 0.005 * min(1.0, (dx / 0.5) ** 4)
+    u0 = workloads.smoothed_noise(n, seed=5)
+    if field == "zeros":
+        u0[700:1500] = 0.0
+    elif field == "tiny":
+        u0[700:1500] *= 2.0 ** -380
+    elif field == "large":
+        u0[1000] = 1e31
+    c = workloads.white_noise(n, seed=6)
+    if cot == "spikes":
+        c[:] = 0.0
+        c[[0, 2000, n - 1]] = 1.0
+    elif cot == "subnormal":
+        c *= 2.0 ** -1060
+    elif cot == "huge":
+        c *= 1e250
+    elif cot == "mixed":
+        c[1000:1100] *= 1e250
+        c[3000:3100] *= 2.0 ** -1060
+    elif cot == "nan":
+        c[1234] = np.nan
+    g = sw.adjoint(torch.from_numpy(u0).cuda(), nsteps, "ks", [dt, dx], window_first=20,
+                   window_weight=weight, cot_final=torch.from_numpy(c).cuda())
+    torch.cuda.synchronize()
+    want = oracle_mod.ks_adjoint(u0, nsteps, dt, dx, 20, weight, c)
+    assert same_up_to_nan(g.cpu().numpy(), want)
+
+
 @pytest.mark.parametrize("stencil,n,nsteps,first", [
     ("heat", 1000, 40, 30), ("ks", 4099, 2100, 2), ("ks_fma", 300, 9, 0), ("heat_fma", 65536, 400, 100),
 ])
