@@ -36,6 +36,11 @@ HEAT_OPS_PER_UPDATE = 5           # add, mul, sub, mul, add (no fused multiply-a
 HEAT_FUSED_LAP_OPS = 4
 HEAT_FMA_OPS_PER_UPDATE = 3       # add, fma, fma (the contraction-on stencil)
 KS_FMA_OPS_PER_STEP = 22          # 3 + 8 + 3 + 8 instructions per point-step, fused
+# Register windows issue fewer where constants are powers of two (the
+# workloads' r = 1/4, c1 = 1, c2 = 4), with the same bits: heat add, fma, fma;
+# KS 2 x (2 + 8), contraction-on 2 x (2 + 7).
+WINDOW_KIND = 4                   # stage_times' kind of a window stage
+HEAT_WINDOW_OPS, KS_WINDOW_OPS, KS_FMA_WINDOW_OPS = 3, 20, 18
 # LDS: 128 bytes per clock per CU (the CDNA3 ISA figure; the CDNA4 LDS is
 # 160 KB per CU, its rate taken as the same)
 LDS_PEAK = CUS * 128 * CLOCK_HZ
@@ -103,7 +108,7 @@ def timed_runs(sw, torch, fn, u0, nsteps, params, reps, warmup, after=None, sten
 
 
 KERNEL_SOURCES = [os.path.join(ROOT, "paper_1504_01380_amd", "csrc", f)
-                  for f in ("kernels.hpp", "stencils.hpp")]
+                  for f in ("kernels.hpp", "stencils.hpp", "window.hpp")]
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_heat_f64.json")
 
 
@@ -203,10 +208,23 @@ KS_OPS_PER_STEP = 30  # per point-step: 4 sub-timesteps (4 + 11 + 4 + 11 flops, 
 EULER_OPS_PER_STEP = 320
 
 
-def heat_ops(sw) -> int:
-    """VALU instructions per heat update of the last swept_advance call: 4
-    in the fused-Laplacian form, 5 in the canonical one."""
-    return HEAT_FUSED_LAP_OPS if sw.last_heat_form() == sw.FORM_FUSED else HEAT_OPS_PER_UPDATE
+def heat_ops(sw, windows: bool) -> int:
+    """VALU instructions per heat update (r = 1/4) of the last swept_advance
+    call: 3 on register windows, 4 in the fused-Laplacian form of the swept
+    kernels, 5 in the canonical form of either."""
+    if sw.last_heat_form() != sw.FORM_FUSED:
+        return HEAT_OPS_PER_UPDATE
+    return HEAT_WINDOW_OPS if windows else HEAT_FUSED_LAP_OPS
+
+
+def on_windows(sw, u, nsteps, stencil, par) -> bool:
+    """Whether advance() runs this call on register windows (from the stage
+    kinds of one untimed run on a copy)."""
+    sw.set_profiling(True)
+    sw.advance(u.clone(), nsteps, stencil, par)
+    _, kind = sw.stage_times()
+    sw.set_profiling(False)
+    return set(kind) == {WINDOW_KIND}
 
 
 def other_workloads(sw, torch, workloads, tune=True):
@@ -232,6 +250,10 @@ def other_workloads(sw, torch, workloads, tune=True):
         rec = {"n": n, "time_steps": nsteps, "tile_w": plan["tile_w"],
                "pairs_per_lane": plan["pairs_per_lane"], "stages": plan["stages"],
                "mode": plan["mode"], "tuning": tuned}
+        # (the swept tiling above is what runs only if the windows do not)
+        windows = rec["windows"] = on_windows(sw, u0, nsteps, st, par)
+        if windows and st == "ks":
+            ops = KS_WINDOW_OPS
         for label, fn, reps in (("swept", sw.advance, 3), ("naive", sw.naive_advance, 1)):
             u = u0.clone()
             fn(u, nsteps, st, par)           # warm-up
@@ -249,7 +271,8 @@ def other_workloads(sw, torch, workloads, tune=True):
             rec[label] = n * nsteps / t
             rec[label + "_ms"] = t * 1e3
             if label == "swept" and st == "heat":
-                ops = heat_ops(sw)
+                ops = heat_ops(sw, windows)
+            if label == "swept":
                 rec["ops_per_update"] = ops
         rec["speedup_vs_naive"] = rec["swept"] / rec["naive"]
         rec["swept_frac_alu"] = ops * rec["swept"] / VALU_LANE_OPS
@@ -447,6 +470,7 @@ def fma_legs(sw, torch, workloads, u0, u_canonical, nsteps, updates, tune=True):
     out = {}
     tune_h = sw.autotune(u0.numel(), nsteps, "heat_fma", [0.25], torch.float64) if tune else None
     plan = sw.plan(u0.numel(), nsteps, "heat_fma", torch.float64)
+    win_h = on_windows(sw, u0, nsteps, "heat_fma", [0.25])
     st, uf = timed_runs(sw, torch, sw.advance, u0, nsteps, [0.25], 2, 1, stencil="heat_fma")
     nt, _ = timed_runs(sw, torch, sw.naive_advance, u0, nsteps, [0.25], 1, 1, stencil="heat_fma")
     v = updates / (sum(st) / len(st))
@@ -456,6 +480,7 @@ def fma_legs(sw, torch, workloads, u0, u_canonical, nsteps, updates, tune=True):
                        "swept_frac_alu": HEAT_FMA_OPS_PER_UPDATE * v / VALU_LANE_OPS,
                        "bits_equal_canonical": bool(torch.equal(uf.view(torch.int64),
                                                                 u_canonical.view(torch.int64))),
+                       "windows": win_h,
                        "tile_w": plan["tile_w"], "pairs_per_lane": plan["pairs_per_lane"],
                        "tuning": tune_h}
     del uf
@@ -465,13 +490,15 @@ def fma_legs(sw, torch, workloads, u0, u_canonical, nsteps, updates, tune=True):
     n, ns = k0.numel(), wk["nsteps"]
     tune_k = sw.autotune(n, ns, "ks_fma", par) if tune else None
     plan = sw.plan(n, ns, "ks_fma")
+    win_k = on_windows(sw, k0, ns, "ks_fma", par)
+    ops_k = KS_FMA_WINDOW_OPS if win_k else KS_FMA_OPS_PER_STEP
     st, _ = timed_runs(sw, torch, sw.advance, k0, ns, par, 3, 1, stencil="ks_fma")
     nt, _ = timed_runs(sw, torch, sw.naive_advance, k0, ns, par, 1, 1, stencil="ks_fma")
     v = n * ns / (sum(st) / len(st))
     nv = n * ns / nt[0]
     out["ks"] = {"swept": v, "naive": nv, "speedup_vs_naive": v / nv,
-                 "ops_per_point_step": KS_FMA_OPS_PER_STEP,
-                 "swept_frac_alu": KS_FMA_OPS_PER_STEP * v / VALU_LANE_OPS,
+                 "ops_per_point_step": ops_k,
+                 "swept_frac_alu": ops_k * v / VALU_LANE_OPS, "windows": win_k,
                  "tile_w": plan["tile_w"], "pairs_per_lane": plan["pairs_per_lane"],
                  "tuning": tune_k}
     sw.sync()
@@ -479,19 +506,17 @@ def fma_legs(sw, torch, workloads, u0, u_canonical, nsteps, updates, tune=True):
 
 
 def profile_mix(sw, torch, workloads):
-    """One swept run of each single-field stencil in its tuned launch shape,
-    for counter collection (nothing is timed or printed but progress)."""
+    """One run of each single-field stencil on the automatic schedule, for
+    counter collection (nothing is timed or printed but progress)."""
     we, wk = workloads.WORKLOADS["euler"], workloads.WORKLOADS["ks"]
-    for name, st, nsteps, par, W, P in (
-            ("heat_large", "heat", 2000, [0.25], 1024, 4),
-            ("ks", "ks", 1000, [wk["dt"], wk["dx"]], 1024, 4),
-            ("euler", "euler", 300, [we["cfl"] / we["n"], 1.0 / we["n"], we["gamma"]], 256, 1)):
-        sw.set_tuning(W, P, sw.MODE_AUTO)
+    for name, st, nsteps, par in (
+            ("heat_large", "heat", 2000, [0.25]),
+            ("ks", "ks", 1000, [wk["dt"], wk["dx"]]),
+            ("euler", "euler", 300, [we["cfl"] / we["n"], 1.0 / we["n"], we["gamma"]])):
         u = torch.from_numpy(workloads.initial(name)).cuda()
         sw.advance(u, nsteps, st, par)
         torch.cuda.synchronize()
         progress("%s done" % name)
-    sw.set_tuning(0, 0, sw.MODE_AUTO)
 
 
 def tile_sweep(sw, torch, workloads, args):
@@ -604,54 +629,68 @@ def main():
     # the full diamonds strictly below the target level (the continuous
     # kernel's stages; a diamond whose apex is the target level is banded)
     full = [s for s in range(1, plan["stages"]) if (s - 1) * k + 2 * k - 1 < nsteps]
-    diamond_ms, stage_ms, kinds = [], [], set()
+    launch_ms, stage_ms, kinds, stages = [], [], set(), set()
 
     def record():
         ms, kind = sw.stage_times()
         stage_ms.append(sum(ms))
-        diamond_ms.extend(ms[s] for s in full)
-        kinds.update(kind[s] for s in full)
+        stages.add(len(ms))
+        picked = range(len(ms)) if set(kind) == {WINDOW_KIND} else full
+        launch_ms.extend(ms[s] for s in picked)
+        kinds.update(kind[s] for s in picked)
 
     times, u_swept = timed_runs(sw, torch, sw.advance, u0, nsteps, [0.25], args.steps,
                                 args.warmup, after=record)
     sw.set_profiling(False)
-    ops = heat_ops(sw)     # the form the timed runs took (both give the same bits)
+    windows = kinds == {WINDOW_KIND}
+    ops = heat_ops(sw, windows)     # the form the timed runs took (both give the same bits)
     progress("heat f64 swept runs done (%d VALU instructions per update)" % ops)
     t = sum(times) / len(times)
     updates = float(n) * nsteps
     value = updates / t
 
-    # Dominant kernel: the one that runs the full diamond stages (the
-    # continuous-band kernel when k is a multiple of its band), one launch per
-    # stage; each launch computes 2k^2 point-updates per tile.
-    tiles = plan["tiles"]
-    kname = ("swept_diamond_cont_kernel<Heat<double>,%d>" if kinds == {1} else
-             "swept_stage_kernel<Heat<double>,%d>") % plan["pairs_per_lane"]
-    updates_per_launch = float(tiles) * 2 * k * k
+    # Dominant kernel, one launch per stage.  Register windows: every stage
+    # advances the whole field by its share of the steps, which passes once
+    # through HBM each way; nothing is staged in LDS at these window sizes.
+    # The swept schedule: the kernel that runs the full diamond stages (the
+    # continuous-band kernel when k is a multiple of its band); each launch
+    # computes 2k^2 point-updates per tile.
+    avg_launch = (sum(launch_ms) / len(launch_ms) / 1e3) if launch_ms else float("nan")
+    n_stages = max(stages) if stages else plan["stages"]
+    if windows:
+        kname = "window_kernel<Heat<double>>"
+        updates_per_launch = updates / n_stages
+        algorithmic_bytes = 16.0 * n
+        lds_bytes = 0.0
+    else:
+        tiles = plan["tiles"]
+        kname = ("swept_diamond_cont_kernel<Heat<double>,%d>" if kinds == {1} else
+                 "swept_stage_kernel<Heat<double>,%d>") % plan["pairs_per_lane"]
+        updates_per_launch = float(tiles) * 2 * k * k
+        algorithmic_bytes = float(tiles) * 4 * 2 * k * 8   # RE in/out + LE in/out, 2k values each
+        # LDS per region and stage of the continuous kernel: the right V edge
+        # in (2k points), the new left edge out (2k), and per wave step (nb*k +
+        # NB of them, NB = 64P) slot 0's read of pair -1 and the last slot's
+        # write of its pair (4 points)
+        NB = 64 * plan["pairs_per_lane"]
+        lds_bytes = float(tiles) * 8 * (4 * k + 4 * ((k // max(NB, 1)) * k + NB))
     flops_per_launch = ops * updates_per_launch
-    avg_launch = (sum(diamond_ms) / len(diamond_ms) / 1e3) if diamond_ms else float("nan")
     achieved = flops_per_launch / avg_launch
-    edge_bytes = float(tiles) * 4 * 2 * k * 8   # RE in/out + LE in/out, 2k values each
-    # LDS per region and stage of the continuous kernel: the right V edge
-    # in (2k points), the new left edge out (2k), and per wave step (nb*k + NB
-    # of them, NB = 64P) slot 0's read of pair -1 and the last slot's write
-    # of its pair (4 points)
-    NB = 64 * plan["pairs_per_lane"]
-    lds_bytes = float(tiles) * 8 * (4 * k + 4 * ((k // max(NB, 1)) * k + NB))
     lds = {"achieved_GBps": lds_bytes / avg_launch / 1e9, "peak_GBps": LDS_PEAK / 1e9,
            "frac": lds_bytes / avg_launch / LDS_PEAK, "bytes_per_launch": lds_bytes,
            "kernel": kname}
     roofline = {"bound": "alu", "achieved": achieved / 1e12, "peak": VALU_LANE_OPS / 1e12,
                 "unit": "TFLOP/s", "frac": achieved / VALU_LANE_OPS,
                 "traffic": measured_traffic(kname),
-                "kernel": kname, "launches_per_step": len(diamond_ms) // max(1, args.steps),
-                "stages_per_step": plan["stages"], "avg_launch_ms": avg_launch * 1e3,
+                "kernel": kname, "launches_per_step": len(launch_ms) // max(1, args.steps),
+                "stages_per_step": n_stages, "avg_launch_ms": avg_launch * 1e3,
                 "flops_per_launch": flops_per_launch, "ops_per_update": ops,
-                "heat_form": "fused Laplacian" if ops == HEAT_FUSED_LAP_OPS else "canonical",
+                "heat_form": {HEAT_WINDOW_OPS: "exact product", HEAT_FUSED_LAP_OPS:
+                              "fused Laplacian"}.get(ops, "canonical"),
                 "counting": "FP64 VALU instructions issued per update (a fused multiply-add "
                             "issues once)",
                 "stage_sum_ms": sum(stage_ms) / max(1, len(stage_ms)),
-                "algorithmic_bytes_per_launch": edge_bytes,
+                "algorithmic_bytes_per_launch": algorithmic_bytes,
                 "whole_run_frac": ops * value / VALU_LANE_OPS}
 
     out = {
@@ -660,8 +699,10 @@ def main():
         "warmup": args.warmup, "ms_per_step": t * 1e3, "higher_is_better": True,
         "scaling": "weak", "vs_baseline": None, "dtype": "f64", "data": "synthetic",
         "config": {"workload": "heat N=2^24 f64 r=0.25 20000 steps, u0~U[-1,1] seed 1001",
-                   "n": n, "time_steps": nsteps, "tile_w": plan["tile_w"],
-                   "depth_k": plan["depth_k"], "tiles": plan["tiles"], "stages": plan["stages"],
+                   "n": n, "time_steps": nsteps,
+                   "schedule": "register windows" if windows else "swept", "stages": n_stages,
+                   # the swept tiling (what runs if the windows do not)
+                   "tile_w": plan["tile_w"], "depth_k": plan["depth_k"], "tiles": plan["tiles"],
                    "pairs_per_lane": plan["pairs_per_lane"], "tuning": tuning},
         "roofline": roofline,
         "lds": lds,
@@ -697,12 +738,13 @@ def main():
         tune32 = None if args.no_tune else sw.autotune(n, nsteps, "heat", [0.25], torch.float32)
         plan32 = sw.plan(n, nsteps, "heat", torch.float32)
         st, _ = timed_runs(sw, torch, sw.advance, u32, nsteps, [0.25], 2, 1)
-        ops32 = heat_ops(sw)
+        win32 = on_windows(sw, u32, nsteps, "heat", [0.25])
+        ops32 = heat_ops(sw, win32)
         nt32, _ = timed_runs(sw, torch, sw.naive_advance, u32, nsteps, [0.25], 1, 1)
         s32 = updates / (sum(st) / len(st))
         n32 = updates / nt32[0]
         out["f32"] = {"swept": s32, "naive": n32, "speedup_vs_naive": s32 / n32,
-                      "ops_per_update": ops32,
+                      "ops_per_update": ops32, "windows": win32,
                       "swept_frac_alu": ops32 * s32 / VALU_LANE_OPS_F32,
                       "naive_hbm_frac": n32 * HEAT_NAIVE_BYTES[4] / HBM_PEAK,
                       "tile_w": plan32["tile_w"], "pairs_per_lane": plan32["pairs_per_lane"],

@@ -337,7 +337,8 @@ def set_profiling(enable: bool) -> None:
 
 def stage_times():
     """(ms, kind) per stage launch of the most recent profiled swept_advance;
-    kind 0 = banded kernel (triangle or capped stage), 1 = continuous kernel."""
+    kind 0 = banded kernel (triangle or capped stage), 1 = continuous kernel,
+    2 = lane-frame kernel, 3 = unequal tiling, 4 = register windows."""
     count = ctypes.c_int64(0)
     _check(_lib.swept_stage_times(None, None, 0, ctypes.byref(count)), "swept_stage_times")
     n = count.value

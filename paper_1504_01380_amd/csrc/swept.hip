@@ -2005,7 +2005,9 @@ int window_keep(const typename S::T* in, typename S::T* kept, int64_t nx, int64_
     return SWEPT_OK;
 }
 
-// operations of a point in one transposed KS step (window_adjoint_kernel)
+// A transposed KS step in the plan's measure (WindowCost::per): its 40 operations
+// a point wait for one another and for their field's loads, and a row of three
+// points a lane takes 0.45 us (window_adjoint_kernel)
 constexpr int kAdjOps = 62;
 
 template <class S, int... MS>

@@ -21,10 +21,22 @@
 // halo, 2*halo of 64*M columns, which deep registers (M up to 48 for heat)
 // make small.  Against the diamonds of swept_diamond_cont_kernel, whose
 // fill and drain idle a fifth of its slots and whose lane-0 chain, band
-// changes and hand-on moves take another 16% of the issue: heat f64 at 2^24
-// points 6.2e12 -> 7.8e12 point-updates/s with the same four operations per
-// update, 9.9e12 with three (HeatExact below); 4096 points 225 -> 67 ns per
-// step (one wave per SIMD and no two-rows-per-level diamond).
+// changes and hand-on moves take another 16% of the issue (point-steps/s, or
+// time of a step, on MI355X):
+//   heat f64, 2^24 points   6.2e12 -> 7.8e12 with the same four operations per
+//                           update, 1.0e13 with three (HeatExact below)
+//   heat f64, 4096 points   225 -> 54 ns (one wave per SIMD, no two-rows-per-
+//                           level diamond)
+//   heat f32, 2^22 points   6.6e12 -> 1.4e13
+//   KS, 2^20 points         4.8e11 -> 1.08e12;  4096 points 1.21 -> 0.26 us
+//   Euler, 2^20 cells       2.3e10 -> 8.8e10;  4096 cells 8.7 -> 1.04 us
+// What is left, by the counters: heat at 2^24 points issues vector
+// instructions in 90% of its clocks, 96% of them FP64.  KS at 2^20 points is one
+// wave a SIMD, which issues in 85% of the clocks of its rows; a fifth of each
+// launch is its start, its first loads and its last stores, which no other
+// wave's rows cover (two waves of half the window cover them, but the halo is
+// twice the part of a window: 1.08 us a step against 1.00).  Small grids are the
+// latency of a row (M points and two DPP moves in a chain) and 2.2 us a launch.
 #pragma once
 
 #include <limits>
@@ -313,7 +325,7 @@ __device__ __forceinline__ bool ks_rows(double (&u)[M], int steps, const KSF64::
 // bounded by the registers of nine values a cell.  Against the diamonds (two
 // waves per SIMD, a fifth of the slots in fill and drain; 4096 cells: two rows
 // a level): 2^20 cells 2.3e10 -> 5.7e10 cell-steps/s untuned (4.2e10 tuned),
-// 4096 cells 8.7 -> 1.7 us a step.
+// 4096 cells 8.7 -> 1.7 us a step (euler_half below takes both further).
 template <class S, int PH, int M>
 __device__ __forceinline__ void window_phase(typename S::Pt (&P)[M], const typename S::Consts& c)
 {
@@ -343,7 +355,8 @@ __device__ __forceinline__ void window_phase(typename S::Pt (&P)[M], const typen
 }
 
 // The same step with the same bits from 300 instruction slots a cell instead of
-// 490 (2^20 cells: 19.1 -> 12.6 us a step; 4096: 1.56 -> 1.05), for states far
+// 490 (2^20 cells: 19.1 -> 12.6 us a step, 11.9 in stages of 4 steps instead of
+// 3; 4096: 1.56 -> 1.04), for states far
 // from the ends of the exponent range (EulerRange):
 //  - halvings are exact, so 0.5*x + y is fma(0.5, x, y), and faces are kept as
 //    2F with the half moved into the step's coefficient;
