@@ -7,7 +7,7 @@ import subprocess
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 SRC = os.path.join(PKG, "csrc", "swept.hip")
-DEPS = [os.path.join(PKG, "csrc", f) for f in ("stencils.hpp", "kernels.hpp", "window.hpp")] + \
+DEPS = [os.path.join(PKG, "csrc", f) for f in ("stencils.hpp", "kernels.hpp", "window.hpp", "stages.hpp")] + \
     [os.path.join(ROOT, "include", h) for h in ("swept.h", "swept_debug.h")]
 LIB = os.path.join(PKG, "libswept.so")
 LIB_COUNT = os.path.join(PKG, "libswept_count.so")

@@ -23,6 +23,7 @@
 #include "swept_debug.h"
 #include "kernels.hpp"
 #include "window.hpp"
+#include "stages.hpp"
 
 // Scratch of swept_advance_noalloc: a fixed array that every GPU the library
 // runs on holds until the process ends.  Host code never uses its name as an
@@ -1798,12 +1799,6 @@ WindowShape window_shape(const int (&sizes)[N], int id, int ops)
     return best;
 }
 
-// time steps done before stage s of a plan: the run spread evenly over its stages
-[[maybe_unused]] int64_t stage_start(int64_t nsteps, int64_t stages, int64_t s)
-{
-    return nsteps / stages * s + nsteps % stages * s / stages;
-}
-
 template <class S, bool ALL = false, int... MS>
 void launch_window_of(const WindowArgs<S>& a, int M, hipStream_t st, std::integer_sequence<int, MS...>)
 {
@@ -2024,11 +2019,10 @@ void launch_window_adjoint(const WindowAdjArgs<S>& a, int M, std::integer_sequen
 }
 
 // The adjoint on windows (window_adjoint_kernel).  The fields the reverse sweep
-// reads are kept from a forward pass: KS every step's, heat those of the
-// objective's window; heat's transposed step below the window (or without
-// one) reads no field and is the forward step itself, so that part of the
-// reverse sweep is a run of the cotangent.  Scratch: the kept fields and two
-// cotangents; SWEPT_ENOMEM, before anything is enqueued, if that cannot be had.
+// reads are kept from a forward pass (adjoint_run); heat's reverse sweep below
+// the objective's window, or without one, is a forward run of the cotangent.
+// Scratch: the kept fields and two cotangents; SWEPT_ENOMEM, before anything is
+// enqueued, if that cannot be had.
 template <class S>
 int run_window_adjoint(const typename S::T* u0, typename S::T* grad, int64_t nx, int64_t nsteps,
                        int id, const typename S::Consts& c, int64_t win_first, double wgt,
@@ -2036,11 +2030,8 @@ int run_window_adjoint(const typename S::T* u0, typename S::T* grad, int64_t nx,
 {
     using T = typename S::T;
     constexpr bool ks = is_ks<S>;
-    const int64_t from = std::max<int64_t>(win_first, 0);       // first step with a source
-    const bool windowed = from <= nsteps;
-    // steps whose fields are kept: kept0 .. nsteps
-    const int64_t kept0 = ks ? 1 : std::max<int64_t>(from, 1);
-    const int64_t nkept = ks || windowed ? nsteps - kept0 + 1 : 0;
+    const AdjointRun run = adjoint_run(ks, nsteps, win_first);
+    const int64_t kept0 = run.kept0, nkept = run.nkept;
     const size_t field = ((size_t)nx * sizeof(T) + 255) / 256 * 256;
     if ((double)nkept * (double)nx * sizeof(T) > 1e14)
         return fail(SWEPT_ENOMEM, "the adjoint would keep %lld fields", (long long)nkept);
@@ -2077,11 +2068,10 @@ int run_window_adjoint(const typename S::T* u0, typename S::T* grad, int64_t nx,
     }
 
     // reverse, down to the first step whose field is read (at least the seed)
-    const int64_t stop = ks ? 0 : std::min(from, nsteps);
-    const int64_t total = nsteps - stop;
+    const int64_t stop = run.stop, total = nsteps - stop;
     const T* in = cot;
     int flip = 0;
-    if (windowed || ks || cot == nullptr) {
+    if (run.windowed || ks || cot == nullptr) {
         WindowShape shape = window_shape(kWindowAdj, id, ks ? kAdjOps : 6);
         if (ks)
             shape.extra = 2;
@@ -2095,26 +2085,24 @@ int run_window_adjoint(const typename S::T* u0, typename S::T* grad, int64_t nx,
         a.n = nx;
         a.own = p.own;
         a.tiles = (int)p.tiles;
-        a.win_first = win_first;
+        a.win_first = run.win_first;
         a.two_w = (T)(2.0 * wgt);
         a.c = c;
         if constexpr (ks)   // ks_adj_quick's conditions on the constants
             a.quick = form.exact && c.c1 >= 1.0 && std::fabs(a.two_w) <= 1e60;
-        int64_t done = 0;
+        a.halo = p.halo;
         for (int64_t s = 0; s < p.stages; ++s) {
-            const int64_t upto = stage_start(total, p.stages, s + 1);
-            if (upto == done && (total > 0 || s > 0))
-                continue;   // no steps, and not the seed alone
-            a.steps = (int)(upto - done);
-            a.halo = p.halo;
-            a.seed = done == 0;
-            a.first = nsteps - upto;
+            const AdjointStage st = adjoint_stage_at(run, nsteps, p.stages, s);
+            if (st.empty)
+                continue;
+            a.steps = (int)st.steps;
+            a.seed = st.seed;
+            a.first = st.first;
             a.in = in;
             a.out = a.first == 0 ? grad : lam[flip];
             launch_window_adjoint<S>(a, p.M, std::integer_sequence<int, 2, 3, 4, 6, 8>{});
             in = a.out;
             flip ^= 1;
-            done = upto;
         }
         HIP_TRY(hipGetLastError());
     }

@@ -855,7 +855,7 @@ struct WindowAdjArgs {
     int tiles, halo, steps;
     int seed;                     // `in` is the objective's cotangent of the final field
     int64_t first;                // time step of `out`
-    int64_t win_first;            // first time step of the objective's window
+    int64_t win_first;            // first time step of the objective's window (stages.hpp)
     typename S::T two_w;          // 2 * objective weight
     int quick;                    // KS: the constants allow ks_adj_quick
     typename S::Consts c;
@@ -1036,11 +1036,14 @@ __device__ __forceinline__ bool adjoint_stage(typename S::T (&lam)[M], const Win
             }
         }
     };
-    // (a field below the stage's steps is not read: the loads stop at `first`)
+    // (a field below the stage's steps is not read: the loads stop at `first`,
+    // and a stage without steps, the seed alone, reads none)
     auto fetch = [&](T (&u)[M], int64_t j) { load(u, field(j > g.first ? j : g.first)); };
+    if (g.steps > 0) {
 #pragma unroll
-    for (int i = 0; i < kSlots; ++i)
-        fetch(f[i], last - 1 - i);
+        for (int i = 0; i < kSlots; ++i)
+            fetch(f[i], last - 1 - i);
+    }
     int64_t j = last - 1;
     for (; j - (kSlots - 1) >= g.first; j -= kSlots) {
 #pragma unroll

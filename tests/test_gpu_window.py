@@ -363,3 +363,25 @@ def test_profiled_stages_are_reported(sw, n, W):
     finally:
         sw.set_tuning(0, 0, sw.MODE_AUTO)
         sw.set_profiling(False)
+
+
+@pytest.mark.parametrize("stencil", ["heat", "ks"])
+@pytest.mark.parametrize("with_cot", [False, True])
+@pytest.mark.parametrize("nsteps", [1, 9])
+def test_adjoint_of_a_window_beyond_the_run(sw, oracle_mod, stencil, nsteps, with_cot):
+    """window_first > nsteps leaves out the window term, however far beyond the
+    last step it lies; without a final cotangent either the gradient is zero."""
+    import torch
+    n = 130
+    u0 = workloads.white_noise(n, seed=n) if stencil == "heat" else workloads.smoothed_noise(n, seed=n)
+    cot = workloads.white_noise(n, seed=1) if with_cot else None
+    par = [0.3] if stencil == "heat" else KS_P
+    oracle = oracle_mod.heat_adjoint if stencil == "heat" else oracle_mod.ks_adjoint
+    want = oracle(u0, nsteps, *par, nsteps + 1, 0.01, cot)
+    for first in (nsteps + 1, nsteps + 2, nsteps + 3, nsteps + 10 ** 6, 2 ** 62, 2 ** 63 - 1):
+        g = sw.adjoint(torch.from_numpy(u0).cuda(), nsteps, stencil, par, window_first=first,
+                       window_weight=0.01,
+                       cot_final=None if cot is None else torch.from_numpy(cot).cuda())
+        torch.cuda.synchronize()
+        assert same_bits(g.cpu().numpy(), want), first
+        assert with_cot or not g.any()
