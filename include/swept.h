@@ -456,7 +456,8 @@ int swept_stage_times(double *ms_out, int32_t *kind_out, int64_t cap, int64_t *c
  *
  * where u^j is the field after j time steps of the stencil, writes dJ/du0 to
  * grad_u0.  u0, grad_u0 and cot_final (NULL = 0) are DEVICE pointers to nx
- * elements; window_first > nsteps leaves out the window term.  The
+ * elements; window_first > nsteps leaves out the window term; grad_u0 may be
+ * the memory of u0 or of cot_final.  The
  * derivative is that of the scheme's sub-timesteps in real arithmetic (each
  * sub-timestep's transposed Jacobian, applied in reverse order), evaluated
  * in a fixed order.

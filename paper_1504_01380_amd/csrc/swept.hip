@@ -2067,6 +2067,16 @@ int run_window_adjoint(const typename S::T* u0, typename S::T* grad, int64_t nx,
             return rc;
     }
 
+    // The last stage reads u0 and the cotangent beyond the points it writes: a
+    // caller's grad that shares memory with either is written from the scratch
+    // when all of it is done (one copy of a field, only for such calls).
+    auto shares = [&](const T* p) {
+        const uintptr_t a = reinterpret_cast<uintptr_t>(grad), b = reinterpret_cast<uintptr_t>(p);
+        const uintptr_t bytes = (uintptr_t)nx * sizeof(T);
+        return p != nullptr && a < b + bytes && b < a + bytes;
+    };
+    const bool in_place = shares(u0) || shares(cot);
+
     // reverse, down to the first step whose field is read (at least the seed)
     const int64_t stop = run.stop, total = nsteps - stop;
     const T* in = cot;
@@ -2099,14 +2109,19 @@ int run_window_adjoint(const typename S::T* u0, typename S::T* grad, int64_t nx,
             a.seed = st.seed;
             a.first = st.first;
             a.in = in;
-            a.out = a.first == 0 ? grad : lam[flip];
+            a.out = a.first == 0 && !in_place ? grad : lam[flip];
             launch_window_adjoint<S>(a, p.M, std::integer_sequence<int, 2, 3, 4, 6, 8>{});
             in = a.out;
             flip ^= 1;
         }
         HIP_TRY(hipGetLastError());
     }
-    return stop > 0 ? window_stages<S>(in, grad, lam[flip], nx, stop, id, c, form, 0) : SWEPT_OK;
+    if (stop > 0)   // (reads `in` into the scratch before it writes grad)
+        return window_stages<S>(in, grad, lam[flip], nx, stop, id, c, form, 0);
+    if (in_place)
+        HIP_TRY(hipMemcpyAsync(grad, in, (size_t)nx * sizeof(T), hipMemcpyDeviceToDevice,
+                               g_ctx.stream));
+    return SWEPT_OK;
 }
 
 #ifdef SWEPT_COUNT_UPDATES

@@ -385,3 +385,33 @@ def test_adjoint_of_a_window_beyond_the_run(sw, oracle_mod, stencil, nsteps, wit
         torch.cuda.synchronize()
         assert same_bits(g.cpu().numpy(), want), first
         assert with_cot or not g.any()
+
+
+@pytest.mark.parametrize("stencil,n,nsteps,first", [
+    ("ks", 20000, 1, 2), ("ks", 20000, 1, 0), ("ks", 70000, 40, 20), ("ks", 64, 3, 4),
+    ("heat", 20000, 1, 0), ("heat", 70000, 60, 0), ("heat", 70000, 60, 30), ("heat", 20000, 9, 10),
+])
+@pytest.mark.parametrize("over", ["u0", "cot"])
+@pytest.mark.parametrize("tile_w", [0, 32])
+def test_adjoint_in_place(sw, stencil, n, nsteps, first, over, tile_w):
+    """The C entry takes u0 or the final cotangent as the gradient's own memory:
+    the same bits as into a field of its own (on windows, and on the swept
+    adjoint, which a tile width asks for)."""
+    import ctypes
+    import torch
+    u0 = torch.from_numpy(workloads.white_noise(n, seed=n)).cuda()
+    cot = torch.from_numpy(workloads.white_noise(n, seed=2)).cuda()
+    par = [0.3] if stencil == "heat" else KS_P
+    want = sw.adjoint(u0, nsteps, stencil, par, window_first=first, window_weight=0.01, cot_final=cot)
+    grad = u0 if over == "u0" else cot
+    arr = (ctypes.c_double * len(par))(*par)
+    sw.set_tuning(tile_w, 0, sw.MODE_AUTO)
+    try:
+        rc = sw.lib().swept_adjoint(u0.data_ptr(), grad.data_ptr(), n, nsteps,
+                                    sw.stencil_id(stencil), arr, len(par), first, 0.01,
+                                    cot.data_ptr())
+    finally:
+        sw.set_tuning(0, 0, sw.MODE_AUTO)
+    assert rc == 0, sw.last_error()
+    torch.cuda.synchronize()
+    assert same_bits(grad.cpu().numpy(), want.cpu().numpy())
