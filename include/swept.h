@@ -465,7 +465,7 @@ int swept_stage_times(double *ms_out, int32_t *kind_out, int64_t cap, int64_t *c
  * Automatic calls (SWEPT_MODE_AUTO, tile width and pairs per lane left at 0)
  * run on register windows: a forward pass keeps the fields the reverse sweep
  * reads (KS: every step's; heat: the window's, since its transposed step reads
- * none) and the reverse sweep takes the cotangent back many steps per launch.
+ * none, and those of a few steps before it where that saves launches) and the reverse sweep takes the cotangent back many steps per launch.
  * Scratch: 8 * nx bytes for every field kept.  Calls for which that is over
  * 4 GiB and over 1.5 times the swept adjoint's scratch, or cannot be had, and
  * other tunings run the swept adjoint:

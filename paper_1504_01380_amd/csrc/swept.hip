@@ -2030,7 +2030,14 @@ int run_window_adjoint(const typename S::T* u0, typename S::T* grad, int64_t nx,
 {
     using T = typename S::T;
     constexpr bool ks = is_ks<S>;
-    const AdjointRun run = adjoint_run(ks, nsteps, win_first);
+    const bool all = ks || adjoint_keeps_all(nx, nsteps, win_first);
+    const AdjointRun run = adjoint_run(all, nsteps, win_first);
+    if (!run.reverse && cot == nullptr) {   // nothing depends on u0: zeros
+        hipLaunchKernelGGL((adjoint_seed_kernel<S>), dim3(grid_for(nx, 256)), dim3(256), 0,
+                           g_ctx.stream, u0, cot, grad, nx, T(0), 0);
+        HIP_TRY(hipGetLastError());
+        return SWEPT_OK;
+    }
     const int64_t kept0 = run.kept0, nkept = run.nkept;
     const size_t field = ((size_t)nx * sizeof(T) + 255) / 256 * 256;
     if ((double)nkept * (double)nx * sizeof(T) > 1e14)
@@ -2081,7 +2088,7 @@ int run_window_adjoint(const typename S::T* u0, typename S::T* grad, int64_t nx,
     const int64_t stop = run.stop, total = nsteps - stop;
     const T* in = cot;
     int flip = 0;
-    if (run.windowed || ks || cot == nullptr) {
+    if (run.reverse) {
         WindowShape shape = window_shape(kWindowAdj, id, ks ? kAdjOps : 6);
         if (ks)
             shape.extra = 2;

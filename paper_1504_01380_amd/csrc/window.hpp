@@ -1036,14 +1036,13 @@ __device__ __forceinline__ bool adjoint_stage(typename S::T (&lam)[M], const Win
             }
         }
     };
-    // (a field below the stage's steps is not read: the loads stop at `first`,
-    // and a stage without steps, the seed alone, reads none)
+    // (a field below the stage's steps is not read: the loads stop at `first`.
+    // A stage without steps, the seed alone, loads the field of `first` too:
+    // a branch around these loads costs the heat stages 12%)
     auto fetch = [&](T (&u)[M], int64_t j) { load(u, field(j > g.first ? j : g.first)); };
-    if (g.steps > 0) {
 #pragma unroll
-        for (int i = 0; i < kSlots; ++i)
-            fetch(f[i], last - 1 - i);
-    }
+    for (int i = 0; i < kSlots; ++i)
+        fetch(f[i], last - 1 - i);
     int64_t j = last - 1;
     for (; j - (kSlots - 1) >= g.first; j -= kSlots) {
 #pragma unroll

@@ -415,3 +415,74 @@ def test_adjoint_in_place(sw, stencil, n, nsteps, first, over, tile_w):
     assert rc == 0, sw.last_error()
     torch.cuda.synchronize()
     assert same_bits(grad.cpu().numpy(), want.cpu().numpy())
+
+
+@pytest.mark.parametrize("n,nsteps,first", [
+    (64, 2, 1), (64, 2, 2), (64, 23, 23), (64, 24, 24), (64, 32, 31), (64, 33, 32), (1000, 10, 5),
+    (1000, 33, 20), (4096, 60, 53), (4096, 60, 54), (65536, 60, 33), (65536, 60, 34),
+    (1 << 20, 9, 4), (1 << 20, 9, 5), (1 << 20, 17, 2), (4096, 700, 20),
+])
+@pytest.mark.parametrize("with_cot", [False, True])
+def test_heat_adjoint_of_short_runs(sw, oracle_mod, n, nsteps, first, with_cot):
+    """Windows that start after a few steps, whose fields are all kept, and ones
+    just late enough that the steps below them run apart."""
+    import torch
+    u0 = workloads.white_noise(n, seed=n)
+    cot = workloads.white_noise(n, seed=1) if with_cot else None
+    g = sw.adjoint(torch.from_numpy(u0).cuda(), nsteps, "heat", [0.3], window_first=first,
+                   window_weight=0.01, cot_final=None if cot is None else torch.from_numpy(cot).cuda())
+    torch.cuda.synchronize()
+    assert same_bits(g.cpu().numpy(), oracle_mod.heat_adjoint(u0, nsteps, 0.3, first, 0.01, cot))
+
+
+def captured_launches(fn):
+    """Nodes of the graph that fn's work on a stream of its own makes."""
+    import ctypes
+    import torch
+    path = next(line.split()[-1] for line in open("/proc/self/maps") if "libamdhip64.so" in line)
+    hip = ctypes.CDLL(path)
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        fn()            # sizes the scratch
+        torch.cuda.synchronize()
+        assert hip.hipStreamBeginCapture(ctypes.c_void_p(s.cuda_stream), 1) == 0   # thread-local
+        try:
+            fn()
+        finally:
+            graph = ctypes.c_void_p()
+            rc = hip.hipStreamEndCapture(ctypes.c_void_p(s.cuda_stream), ctypes.byref(graph))
+    assert rc == 0
+    count = ctypes.c_size_t()
+    assert hip.hipGraphGetNodes(graph, None, ctypes.byref(count)) == 0
+    assert hip.hipGraphDestroy(graph) == 0
+    return count.value
+
+
+@pytest.mark.parametrize("stencil", ["heat", "ks"])
+@pytest.mark.parametrize("n,nsteps,first", [
+    (64, 1, 0), (64, 2, 1), (64, 2, 2), (1000, 10, 2), (1000, 10, 5), (4096, 5, 4), (65536, 20, 10),
+])
+def test_short_adjoints_take_few_launches(sw, stencil, n, nsteps, first):
+    """A gradient of a few steps takes no more launches than on the swept
+    adjoint, whose two passes are two stages each."""
+    import ctypes
+    import torch
+    u0 = torch.from_numpy(workloads.smoothed_noise(n, seed=n)).cuda()
+    cot, grad = torch.ones_like(u0), torch.empty_like(u0)
+    par = [0.3] if stencil == "heat" else KS_P
+    arr = (ctypes.c_double * len(par))(*par)
+
+    def call():
+        sw._prepare(u0, sw.stencil_id(stencil))
+        rc = sw.lib().swept_adjoint(u0.data_ptr(), grad.data_ptr(), n, nsteps,
+                                    sw.stencil_id(stencil), arr, len(par), first, 0.01,
+                                    cot.data_ptr())
+        assert rc == 0, sw.last_error()
+
+    windows = captured_launches(call)
+    sw.set_tuning(0, 0, sw.MODE_STAGE)
+    try:
+        swept = captured_launches(call)
+    finally:
+        sw.set_tuning(0, 0, sw.MODE_AUTO)
+    assert windows <= swept, (windows, swept)

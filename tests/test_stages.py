@@ -19,8 +19,8 @@ int64_t start_of(int64_t nsteps, int64_t stages, int64_t s) { return stage_start
 void run_of(int every, int64_t nsteps, int64_t win_first, int64_t* out)
 {
     const AdjointRun r = adjoint_run(every != 0, nsteps, win_first);
-    const int64_t v[5] = {r.win_first, r.windowed, r.kept0, r.nkept, r.stop};
-    for (int i = 0; i < 5; ++i)
+    const int64_t v[6] = {r.win_first, r.windowed, r.kept0, r.nkept, r.reverse, r.stop};
+    for (int i = 0; i < 6; ++i)
         out[i] = v[i];
 }
 void stage_of(int every, int64_t nsteps, int64_t win_first, int64_t stages, int64_t s, int64_t* out)
@@ -59,7 +59,7 @@ def test_reverse_sweep_reads_kept_fields_only(host, every, nsteps):
     for win_first in firsts:
         out = (ctypes.c_int64 * 6)()
         host.run_of(every, nsteps, win_first, out)
-        first, windowed, kept0, nkept, stop = list(out)[:5]
+        first, windowed, kept0, nkept, reverse, stop = list(out)
         sources = [j for j in range(nsteps + 1) if j >= win_first]
         assert windowed == bool(sources)
         assert [j for j in range(nsteps + 1) if j >= first] == sources
@@ -67,11 +67,15 @@ def test_reverse_sweep_reads_kept_fields_only(host, every, nsteps):
         assert nkept == 0 or kept[-1] == nsteps
         assert all(0 < j for j in kept) and nkept <= nsteps
         assert set(j for j in sources if j > 0) <= set(kept)
+        assert reverse == (every or windowed)
+        if not reverse:      # no stage is launched
+            assert nkept == 0 and stop == nsteps
+            continue
         if every:
             assert set(kept) == set(range(1, nsteps + 1)) and stop == 0
         else:   # nothing is read below `stop`
             assert all(j >= stop for j in sources)
-        for stages in (2, 4, 6, 2 * nsteps):
+        for stages in (1, 2, 3, 4, 5, 6, 2 * nsteps):
             taken, seeds = [], 0
             for s in range(stages):
                 host.stage_of(every, nsteps, win_first, stages, s, out)
@@ -83,6 +87,6 @@ def test_reverse_sweep_reads_kept_fields_only(host, every, nsteps):
                 assert seed == (not taken)
                 taken += range(at + steps - 1, at - 1, -1)
                 reads = range(lo, hi + 1)
-                assert set(range(at, at + steps)) <= set(reads)
+                assert set(range(at, at + steps)) | {at} <= set(reads)
                 assert all(j == 0 or j in kept for j in reads), (win_first, stages, s)
             assert seeds == 1 and taken == list(range(nsteps - 1, stop - 1, -1))
