@@ -2779,9 +2779,16 @@ int run_objective(const void* u0, int64_t nx, int64_t nsteps, int32_t id, const 
                         : 0;
     if (chunk < 4)
         chunk = 0;
-    const size_t part_b = (size_t)chunk * kObjBlocks * sizeof(double);
-    int rc = ensure_obj(field + 4 * kObjBlocks * sizeof(double) + part_b +
-                        (size_t)chunk * (size_t)nx * sizeof(double));
+    auto bytes = [&] {
+        return field + 4 * kObjBlocks * sizeof(double) +
+               (size_t)chunk * (kObjBlocks + (size_t)nx) * sizeof(double);
+    };
+    int rc = ensure_obj(bytes());
+    if (rc == SWEPT_ENOMEM && chunk > 0) {   // one step at a time needs a field only
+        chunk = 0;
+        g_err.clear();
+        rc = ensure_obj(bytes());
+    }
     if (rc)
         return rc;
     double* f = static_cast<double*>(g_ctx.obj);
