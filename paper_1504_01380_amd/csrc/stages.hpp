@@ -10,10 +10,11 @@
 
 namespace swept {
 
-// time steps done before stage s of a plan: the run spread evenly over its stages
+// time steps done before stage s of a plan: the run spread evenly over its
+// stages (the product passes 64 bits from 3e9 stages on)
 inline int64_t stage_start(int64_t nsteps, int64_t stages, int64_t s)
 {
-    return nsteps / stages * s + nsteps % stages * s / stages;
+    return nsteps / stages * s + (int64_t)((__int128)(nsteps % stages) * s / stages);
 }
 
 // What the window adjoint keeps of the forward pass and how far its reverse

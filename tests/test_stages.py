@@ -90,3 +90,15 @@ def test_reverse_sweep_reads_kept_fields_only(host, every, nsteps):
                 assert set(range(at, at + steps)) | {at} <= set(reads)
                 assert all(j == 0 or j in kept for j in reads), (win_first, stages, s)
             assert seeds == 1 and taken == list(range(nsteps - 1, stop - 1, -1))
+
+
+@pytest.mark.parametrize("nsteps,stages", [
+    (1, 2), (7, 4), (40, 6), (20000, 180), (10 ** 12 + 7, 4 * 10 ** 9), (10 ** 15 - 1, 8 * 10 ** 12 + 2),
+    (2 ** 60 - 1, 2 ** 59 + 2),
+])
+def test_stages_share_the_steps_evenly(host, nsteps, stages):
+    """Stage s starts after floor(nsteps * s / stages) steps, also where the
+    product of the two does not fit 64 bits."""
+    at = sorted({0, 1, 2, stages // 3, stages // 2, stages - 2, stages - 1, stages})
+    for s in at:
+        assert host.start_of(nsteps, stages, s) == nsteps * s // stages
