@@ -296,10 +296,11 @@ def other_workloads(sw, torch, workloads, tune=True):
 
 def batch_workload(sw, torch, workloads, tune=True):
     """The ensemble: 4096 independent instances (half heat, half KS, N
-    log-uniform in [256, 65536], 1,000-20,000 steps) in one batched swept
-    run, against the batched naive schedule (one launch per time step over
-    all instances still running).  Rates count each instance's own N x steps
-    (the two-fold cover of an odd ring is overhead, not work)."""
+    log-uniform in [256, 65536], 1,000-20,000 steps) in one batch at the default
+    settings, against the two swept schedules and the batched naive schedule
+    (one launch per time step over all instances still running).  Rates count
+    each instance's own N x steps (halos, and the two-fold cover of an odd ring
+    on the swept schedules, are overhead, not work)."""
     insts = workloads.batch()
     ns = [i.nsteps for i in insts]
     kinds = [i.stencil for i in insts]
@@ -319,8 +320,8 @@ def batch_workload(sw, torch, workloads, tune=True):
             a.copy_(b)
         torch.cuda.synchronize()
 
-    def timed(schedule):
-        sw.set_batch_schedule(schedule, 0)
+    def timed(*settings):
+        sw.set_batch_schedule(*settings)
         t0 = time.perf_counter()
         sw.advance_batch(us, ns, kinds, pars)     # warm-up: plan, capture the graph
         torch.cuda.synchronize()
@@ -337,15 +338,19 @@ def batch_workload(sw, torch, workloads, tune=True):
         sw.sync()
         return sorted(ts)[1], first
 
-    # one launch per stage first, then the default: one persistent launch
-    ts_, _ = timed(sw.BATCH_STAGED)
-    rec["staged"] = work / ts_
-    rec["staged_ms"] = ts_ * 1e3
-    t, rec["first_call_s"] = timed(sw.BATCH_PERSISTENT)
-    rec["schedule"] = "persistent (one launch, per-tile stage flags)"
+    # the two swept schedules (a number of tasks per claim, the library's own
+    # default here, asks for the persistent launch), then the default settings
+    staged, _ = timed(sw.BATCH_STAGED, 0)
+    persistent, _ = timed(sw.BATCH_PERSISTENT, 0, 2)
+    t, rec["first_call_s"] = timed(sw.BATCH_PERSISTENT, 0)
+    for name, sec in (("staged", staged), ("persistent", persistent)):
+        rec[name], rec[name + "_ms"] = work / sec, sec * 1e3
+    rec["schedule"] = "default settings: register windows (two chains of launches)" + \
+        (", unless the tuner measured a swept schedule faster" if tune else "")
     rec["swept"] = work / t
     rec["swept_ms"] = t * 1e3
-    rec["persistent_vs_staged"] = ts_ / t
+    rec["persistent_vs_staged"] = staged / persistent
+    rec["default_vs_persistent"] = persistent / t
     rec["heat_form"] = "fused-Laplacian" if sw.last_heat_form() == sw.FORM_FUSED else "canonical"
     sw.naive_advance_batch(us[:64], [min(x, 4) for x in ns[:64]], kinds[:64], pars[:64])
     restore()
