@@ -70,9 +70,9 @@ def parse():
                          "autotuned swept against naive, one JSON line each (instead of the "
                          "benchmark line)")
     ap.add_argument("--profile-mix", action="store_true",
-                    help="short run for rocprofv3 instruction counters: one swept run each of "
-                         "heat (2^24, 2,000 steps, W=1024 P=4), KS (2^20, 1,000 steps, W=1024 "
-                         "P=4) and Euler (2^20 cells, 300 steps, W=256 P=1)")
+                    help="short run for rocprofv3 instruction counters: one automatic run each "
+                         "of heat (2^24, 2,000 steps), KS (2^20, 1,000 steps) and Euler (2^20 "
+                         "cells, 300 steps)")
     return ap.parse_args()
 
 

@@ -183,13 +183,17 @@ int swept_set_tuning(int32_t tile_w, int32_t pairs_per_lane, int32_t mode);
  *    no point comes near MAX/2, the only place where the two forms differ
  *    (2*u overflows, the fused form does not); a non-finite value only
  *    produces non-finite values, alike in both forms.  Otherwise the
- *    kernels evaluate the five operations as written.  Where r is a power of
- *    two, the window kernel also fuses the multiply-add u + r*lap in windows
- *    whose values are large enough that r*lap is exact (three operations).
- *    A batch takes one
- *    decision for all its heat instances: every one must meet the
- *    conditions (its r, its step count, its field), else all of them run
- *    the five operations; each launch of a batch checks its fields again.
+ *    kernels evaluate the five operations as written.
+ *    On the swept schedules the check decides for the whole call, and in a
+ *    batch for all its heat instances: every one must meet the conditions
+ *    (its r, its step count, its field), else all of them run the five
+ *    operations; each launch of a batch checks its fields again.
+ *    On register windows r and the step count decide for the whole call (of a
+ *    batch: for all its heat instances), and the values for each window and
+ *    stage by itself: one large value sends only the windows that hold it to
+ *    the five operations.  Where r is a power of two, a window whose values
+ *    are large enough that r*lap is exact also fuses the multiply-add
+ *    u + r*lap (three operations).
  *  - SWEPT_FORM_CANONICAL: always the five operations as written.
  * The setting persists until changed.  Other stencil ids, swept_naive_advance
  * and the adjoints always evaluate their schemes as written.
@@ -205,7 +209,9 @@ int swept_set_heat_form(int32_t form);
  * The form the last swept_advance or swept_advance_noalloc call with
  * SWEPT_HEAT_F64 or SWEPT_HEAT_F32, or the last swept_advance_batch call with
  * a heat instance, evaluated (SWEPT_FORM_FUSED or SWEPT_FORM_CANONICAL; the
- * naive schedule counts as canonical), or 0 before any such call.  It
+ * naive schedule counts as canonical), or 0 before any such call.  On register
+ * windows SWEPT_FORM_CANONICAL means that r or the step count asked for it, or
+ * that at least one window of the first stage held too large a value.  It
  * synchronises the library's stream to read the device-side check.
  */
 int swept_last_heat_form(int32_t *form);
@@ -213,7 +219,8 @@ int swept_last_heat_form(int32_t *form);
 /*
  * Plan the swept run for these arguments, without running it: the tiling that
  * swept_advance uses for the tunings that run swept stages (the
- * register-window schedule of automatic calls chooses its windows by itself).  out[0..5] = { tile_w, depth_k, tiles, stages, pairs_per_lane
+ * register-window schedule of automatic calls chooses its windows by itself).
+ * out[0..5] = { tile_w, depth_k, tiles, stages, pairs_per_lane
  * (0 on the lane-frame kernel), mode_used }.  For SWEPT_MODE_STAGE_RAGGED
  * tile_w = 2k is the width of the full tiles and tiles counts the tiles of
  * the ring (the two-fold cover for odd nx).  Returns SWEPT_EINVAL for
@@ -229,10 +236,11 @@ int swept_plan(int64_t nx, int64_t nsteps, int32_t stencil_id, int64_t *out);
  * run the register-window schedule: stages of many time
  * steps, each a kernel launch in which every wavefront advances a window of
  * consecutive points in registers, wide enough that the points it owns depend
- * on nothing outside it.  Neighbouring windows overlap, so a few per cent of
- * the updates are computed twice, which costs less than the edges the swept
- * stages exchange; any nx is taken as it is.  Results are the same bits.  It
- * takes nx field elements of scratch.
+ * on nothing outside it.  Neighbouring windows overlap, so updates are computed
+ * more than once: 10 to 25% of them on grids that fill the GPU, several times
+ * as many on small ones, whose windows run where the GPU would idle.  Any nx is
+ * taken as it is.  Results are the same bits.  It takes nx field elements of
+ * scratch.
  *
  * Other tunings run the swept rule.  Its automatic
  * plan tiles every grid: with equal tiles of the largest even width W that
@@ -249,7 +257,7 @@ int swept_advance(void *u, int64_t nx, int64_t nsteps, int32_t stencil_id,
 /*
  * For callers that cannot allocate device memory -- code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc: the same
- * as swept_advance (same arguments, plan, kernels and bits), with the scratch
+ * as swept_advance (same arguments, schedules and bits), with the scratch
  * in a fixed array of SWEPT_NOALLOC_SCRATCH_BYTES that the library holds on
  * each GPU it runs on (from swept_init until the process ends) instead of
  * memory it allocates.  The call allocates nothing.  It is limited to the
@@ -296,9 +304,11 @@ int swept_naive_substep_advance(void *u, int64_t nx, int64_t nsteps, int32_t ste
  * windows: per stage one launch per stencil over the tiles of the instances
  * that still have steps to go, each instance on windows of its own ring (any
  * length, no cover), between its field and a spare copy in the scratch.  The
- * tables of a call pass through pinned host memory without a wait for the work
- * enqueued before; the call cannot be captured into a graph (SWEPT_EHIP).  Other
- * settings run the swept schedules described next.
+ * tables of a call pass through two pinned host buffers in turn: the call
+ * returns before the work enqueued ahead of it is done, but waits until the
+ * tables of the call two before it have been copied, so that back-to-back
+ * batches run at most two ahead of the GPU.  It cannot be captured into a graph
+ * (SWEPT_EHIP).  Other settings run the swept schedules described next.
  *
  * Each instance of 2h points (h = nx/2 for even nx) is tiled by T = ceil(h/k)
  * tiles: T-1 of width 2k and one of the remainder 2(h - (T-1)k) (k =
@@ -310,9 +320,9 @@ int swept_naive_substep_advance(void *u, int64_t nx, int64_t nsteps, int32_t ste
  * odd length runs on its two-fold cover
  * (the field repeated twice, which the scheme keeps repeated).
  *
- * Schedule (swept_set_batch_schedule).  SWEPT_BATCH_PERSISTENT, the default:
- * one persistent kernel launch per stencil runs every region of every stage
- * of every instance.  Its workgroups (as many as the GPU holds at once)
+ * Schedule (swept_set_batch_schedule).  SWEPT_BATCH_PERSISTENT: one persistent
+ * kernel launch per stencil runs every region of every stage of every
+ * instance.  Its workgroups (as many as the GPU holds at once)
  * take regions from device counters, in stage-major order with the
  * instances with the most stages first, and a region waits only for the two
  * regions of the previous stage it reads (its own tile's and the next
@@ -337,7 +347,8 @@ int swept_advance_batch(void *const *u, const int64_t *nx, const int64_t *nsteps
 
 /* Schedules for swept_set_batch_schedule. */
 enum {
-    SWEPT_BATCH_PERSISTENT = 0,   /* one persistent launch for the whole batch (default) */
+    SWEPT_BATCH_PERSISTENT = 0,   /* one persistent launch for the whole batch (default;
+                                     with all defaults the batch runs on windows) */
     SWEPT_BATCH_STAGED = 1        /* one launch per stage and stencil */
 };
 
@@ -420,8 +431,8 @@ int swept_autotune(int64_t nx, int64_t nsteps, int32_t stencil_id, const double 
  * schedule, best of two runs each, choosing the depth k in {128, 256, 384,
  * 512} for KS and then for heat (each with the other's depth set, since the
  * two stencils' launches overlap), and keeps the choice for later batches, or
- * the register windows where they run the same probe faster.  depth_out (host, 3 entries indexed by stencil id)
- * receives the chosen depth, 0 for a stencil not in the batch.  Allocates
+ * the register windows where they run the same probe faster.  depth_out (host,
+ * 3 entries indexed by stencil id) receives the chosen depth, 0 for a stencil not in the batch.  Allocates
  * and frees its own probe fields; synchronizes the stream.
  */
 int swept_autotune_batch(const int64_t *nx, const int64_t *nsteps, const int32_t *stencil_id,
@@ -466,9 +477,11 @@ int swept_stage_times(double *ms_out, int32_t *kind_out, int64_t cap, int64_t *c
  * run on register windows: a forward pass keeps the fields the reverse sweep
  * reads (KS: every step's; heat: the window's, since its transposed step reads
  * none, and those of a few steps before it where that saves launches) and the reverse sweep takes the cotangent back many steps per launch.
- * Scratch: 8 * nx bytes for every field kept.  Calls for which that is over
- * 4 GiB and over 1.5 times the swept adjoint's scratch, or cannot be had, and
- * other tunings run the swept adjoint:
+ * Scratch: 8 * nx bytes for every field kept, which like all scratch stays
+ * allocated until swept_finalize (or a swept_init of another device).  Calls
+ * for which that is over 4 GiB and over 1.5 times the swept adjoint's scratch,
+ * or cannot be had, and other tunings (a tile width, say, for callers short of
+ * memory) run the swept adjoint:
  *
  * A forward swept pass keeps the V edges of every stage (one checkpoint per
  * sweep, 2*nx points per stage; u0 is only read); the stages then run in
@@ -505,15 +518,17 @@ int swept_naive_adjoint(const void *u0, void *grad_u0, int64_t nx, int64_t nstep
  *
  * written as one double to J_out (a DEVICE pointer), asynchronously on the
  * current stream.  u0 and cot_final (NULL = 0) are DEVICE pointers to nx
- * doubles; u0 is only read.  A copy of u0 advances by the swept schedule to
+ * doubles; u0 is only read.  A copy of u0 advances as by swept_advance to
  * the step before the window, then one naive launch per step of the window
  * (the sum needs every one of its fields).  Each step's sum is formed on the
  * device in a fixed order and the steps are accumulated with compensated
  * (two-sum) addition, so J does not depend on timing and its relative
  * rounding error is a few units of 1e-16 rather than growing with the number
  * of steps -- what a finite-difference check of the gradient differences.
- * (Automatic calls keep the window's fields, 64 MiB of them at a time, and sum
- * them in the same order, which gives the same J in fewer launches.)
+ * (Automatic calls run the window's steps on register windows, keep their
+ * fields, 64 MiB of them at a time, and sum them in the same order, which gives
+ * the same J in fewer launches; without memory for that they take one naive
+ * step at a time.)
  * Uses its own device buffer (nx doubles, 8 KiB and those fields), grown on
  * demand.
  */

@@ -181,7 +181,8 @@ def set_heat_form(form: int = FORM_AUTO) -> None:
 def last_heat_form() -> int:
     """FORM_FUSED or FORM_CANONICAL: how the last heat advance(), or the
     last advance_batch() with a heat instance, evaluated its updates (0
-    before any); synchronises the library's stream."""
+    before any); on register windows FORM_CANONICAL means that at least one
+    window did as written.  Synchronises the library's stream."""
     out = ctypes.c_int32(0)
     _check(_lib.swept_last_heat_form(ctypes.byref(out)), "swept_last_heat_form")
     return int(out.value)
@@ -192,7 +193,8 @@ def set_batch_schedule(schedule: int = BATCH_PERSISTENT, spin_limit: int = 0,
     """BATCH_PERSISTENT (one launch per stencil for the whole batch) or
     BATCH_STAGED (one launch per stage); for the persistent one, the wait
     limit in microseconds, the task numbers per claim and the number of
-    queues (0: the library's defaults)."""
+    queues (0: the library's defaults).  With all four at their defaults, and
+    no tuning set, advance_batch() runs on register windows instead."""
     _check(_lib.swept_set_batch_schedule(int(schedule), int(spin_limit), int(chunk),
                                          int(queues)), "swept_set_batch_schedule")
 
@@ -271,8 +273,10 @@ def _batch_args(us, nsteps, stencils, params):
 def advance_batch(us: Sequence[torch.Tensor], nsteps: Sequence[int], stencils,
                   params: Sequence[Sequence[float]]) -> None:
     """Advance independent float64 fields in place, instance j by nsteps[j]
-    steps of stencils[j] ("heat" or "ks") with params[j], in one batched
-    swept run (one HIP graph)."""
+    steps of stencils[j] ("heat" or "ks") with params[j], in one batched run:
+    at the default settings on register windows (two chains of launches),
+    otherwise on the swept schedule set_batch_schedule() selects (one HIP
+    graph)."""
     if len(us) == 0:
         return
     _check(_lib.swept_advance_batch(*_batch_args(us, nsteps, stencils, params)),
@@ -439,8 +443,8 @@ def window_mean_square_value(u0: torch.Tensor, nsteps: int, stencil, params, win
 
 
 class WindowMeanSquare(torch.autograd.Function):
-    """J(u0) = mean of u^2 over the final `window` steps; gradient by the
-    swept adjoint with one checkpoint per sweep."""
+    """J(u0) = mean of u^2 over the final `window` steps; gradient by adjoint(),
+    which runs the trajectory again and keeps the fields it reads."""
 
     @staticmethod
     def forward(ctx, u0, nsteps, stencil, params, window):

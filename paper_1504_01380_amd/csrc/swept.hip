@@ -1720,14 +1720,17 @@ WindowShape window_shape(const int (&sizes)[N], int id, int ops)
 // waves of M = 24, 1.51 on four of M = 20), and h rows; 1024 SIMDs share the tiles, and a row takes the longer
 // of a lone wave's time and the issue time of all the waves of a SIMD
 // (WindowCost::many).  Deep stages spread the launch, wide windows the halo;
-// few tiles (small grids) want small windows, whose rows are short.
+// few tiles (small grids) want small windows, whose rows are short.  Where the
+// traffic is taken as half hidden, Euler at 2^20 cells gets windows of 256 cells
+// and 6 steps instead of 384 and 4: 23% of halo instead of 9, the same 11.9 us
+// a step.
 //
 // A call makes its plan anew, while the device waits on a short call, so most
 // pairs of size and depth are left at a bound of their time that takes two
 // divisions: 1.5 us instead of 2.9 at 1000 points and 100 steps, 2.7 instead of
 // 7.2 at 4096 points and 10000.  Depths go in 64ths of the window: in 32nds a
 // 384-cell Euler window had stages of 3 and 6 steps (13.1 and 14.2 us a step
-// at 2^20 cells) but none of 4 (12.2).
+// at 2^20 cells) but none of 4 (11.9).
 [[maybe_unused]] WindowPlan window_plan(const WindowShape& shape, int64_t n, int64_t nsteps)
 {
     struct Depth {
@@ -2217,9 +2220,10 @@ int64_t window_batch_room(const WindowBatchPlan& plan)
 }
 
 // Host tables of a batch on their way to the device: two pinned buffers used in
-// turn, each free again once the copy out of it has run (its event), so that
-// a call neither waits for the work enqueued before it nor overwrites a table
-// that has still to be copied.
+// turn, each free again once the copy out of it has run (its event).  A call
+// does not wait for the work enqueued before it, unless the copy of the call two
+// before has still to run: batches enqueued back to back run at most two ahead
+// of the device.
 struct Staging {
     unsigned char* host[2] = {nullptr, nullptr};
     size_t bytes[2] = {0, 0};
@@ -2765,8 +2769,11 @@ int ensure_obj(size_t bytes)
 }
 
 // J = w * sum_{j = max(first, 0)}^{nsteps} |u^j|^2 + <cot, u^nsteps>: a copy of
-// u0 advanced by the swept schedule to the step before the window, then one
-// naive step at a time, each step's field summed on the device.
+// u0 advanced to the step before the window, then the window's steps, each
+// step's field summed on the device.  Automatic calls take many steps at a time
+// on register windows that keep every step's field (8 us a step at 2^16 points
+// became 1); other settings, and calls without memory for that, one naive step
+// at a time.
 int run_objective(const void* u0, int64_t nx, int64_t nsteps, int32_t id, const double* params,
                   int64_t first, double wgt, const void* cot, double* J)
 {

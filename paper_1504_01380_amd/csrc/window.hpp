@@ -18,8 +18,10 @@
 // What bounds it, and why this shape.  A row costs M point updates and two DPP
 // moves of one point per lane; nothing touches LDS and there is no pipeline to
 // fill, so almost every issued instruction is an update.  The price is the
-// halo, 2*halo of 64*M columns, which deep registers (M up to 48 for heat)
-// make small.  Against the diamonds of swept_diamond_cont_kernel, whose
+// halo, 2*halo of 64*M columns: deep registers (M up to 48 for heat) keep it at
+// 10 to 23% of the owned points on grids that fill the chip.  On small grids it
+// is most of a window (4096 points: 8 times the points for heat, 12 for KS),
+// run by SIMDs that would idle, for stages that are deeper.  Against the diamonds of swept_diamond_cont_kernel, whose
 // fill and drain idle a fifth of its slots and whose lane-0 chain, band
 // changes and hand-on moves take another 16% of the issue (point-steps/s, or
 // time of a step, on MI355X):
@@ -32,10 +34,11 @@
 //   Euler, 2^20 cells       2.3e10 -> 8.8e10;  4096 cells 8.7 -> 1.04 us
 // What is left, by the counters: heat at 2^24 points issues vector
 // instructions in 90% of its clocks, 96% of them FP64.  KS at 2^20 points is one
-// wave a SIMD, which issues in 85% of the clocks of its rows; a fifth of each
-// launch is its start, its first loads and its last stores, which no other
-// wave's rows cover (two waves of half the window cover them, but the halo is
-// twice the part of a window: 1.08 us a step against 1.00).  Small grids are the
+// wave a SIMD: a wave lives 68 thousand clocks and issues in 52 of them (0.77),
+// and no other wave's rows cover its start, its first loads and its last stores
+// (0.75 of a launch of 29 us in a run; 0.56 of the launches that the counters
+// serialise).  Two waves of half the window cover them, but the halo is twice
+// the part of a window: 1.08 us a step against 1.00.  Small grids are the
 // latency of a row (M points and two DPP moves in a chain) and 2.2 us a launch.
 #pragma once
 
@@ -207,6 +210,8 @@ __device__ __forceinline__ void heat_advance(typename S::T (&u)[M], const Window
 //              operation the written one scaled by a power of two.  Needs no
 //              underflow: a scaled result below the smallest normal number
 //              would round where the written one does not.
+// 2^20 points: 1.00 us a step in kKsExact, 1.16 in kKsLap; KSFmaF64 0.97 in
+// kKsExact, 1.03 as written.
 // Both hold for a whole step if 2^-400 <= |u| <= 1e30 at its start and the
 // constants are moderate (window_form: all at most 1e10, and for kKsExact
 // c2 in [1, 2^8], c1 in [2^-8, 2^8]).  From above: |w| <= 4e40, |F| <= 3e70,
@@ -355,9 +360,9 @@ __device__ __forceinline__ void window_phase(typename S::Pt (&P)[M], const typen
 }
 
 // The same step with the same bits from 300 instruction slots a cell instead of
-// 490 (2^20 cells: 19.1 -> 12.6 us a step, 11.9 in stages of 4 steps instead of
-// 3; 4096: 1.56 -> 1.04), for states far
-// from the ends of the exponent range (EulerRange):
+// 490 (2^20 cells: 19.1 -> 12.6 us a step in 384-cell windows of 3 steps, 11.9
+// in windows of 256 cells and 6 steps; 4096: 1.56 -> 1.04), for states far from
+// the ends of the exponent range (EulerRange):
 //  - halvings are exact, so 0.5*x + y is fma(0.5, x, y), and faces are kept as
 //    2F with the half moved into the step's coefficient;
 //  - a/b and sqrt(x) are the sequences the compiler emits for them (Newton steps
