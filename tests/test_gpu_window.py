@@ -486,3 +486,40 @@ def test_short_adjoints_take_few_launches(sw, stencil, n, nsteps, first):
     finally:
         sw.set_tuning(0, 0, sw.MODE_AUTO)
     assert windows <= swept, (windows, swept)
+
+
+@pytest.mark.parametrize("stencil,n,nsteps,first", [
+    ("heat", 4096, 300, 200), ("heat", 4096, 20, 15), ("ks", 4096, 120, 90), ("ks", 1000, 40, 41),
+])
+def test_captured_gradient_and_objective_replay(sw, stencil, n, nsteps, first):
+    """adjoint() and objective() in a captured graph, once their scratch is
+    sized: every replay, on new inputs in the same memory and with eager work
+    and synchronisations between them, equals the eager result."""
+    import torch
+    par = [0.3] if stencil == "heat" else KS_P
+    kw = dict(window_first=first, window_weight=0.01)
+    inputs = [torch.from_numpy(workloads.smoothed_noise(n, seed=s)).cuda() for s in (1, 2, 3)]
+    cot = torch.from_numpy(workloads.white_noise(n, seed=4)).cuda()
+    want = [(sw.adjoint(u, nsteps, stencil, par, cot_final=cot, **kw),
+             sw.objective(u, nsteps, stencil, par, cot_final=cot, **kw)) for u in inputs]
+    torch.cuda.synchronize()
+    u = torch.zeros_like(cot)
+    s = torch.cuda.Stream()
+    s.wait_stream(torch.cuda.current_stream())
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.stream(s):
+        with torch.cuda.graph(graph, stream=s):
+            g = sw.adjoint(u, nsteps, stencil, par, cot_final=cot, **kw)
+            J = sw.objective(u, nsteps, stencil, par, cot_final=cot, **kw)
+    torch.cuda.synchronize()
+    for rep in range(2):
+        for v, (wg, wJ) in zip(inputs, want):
+            u.copy_(v)
+            torch.cuda.synchronize()
+            graph.replay()
+            torch.cuda.synchronize()
+            assert same_bits(g.cpu().numpy(), wg.cpu().numpy()), rep
+            assert float(J) == float(wJ), rep
+            # eager work in the library's own scratch between the replays
+            sw.advance(v.clone(), 7, stencil, par)
+            torch.cuda.synchronize()
