@@ -45,10 +45,16 @@ def build(verbose: bool = False, counting: bool = True) -> str:
     if counting:
         jobs.append(_compile(LIB_COUNT, ["-DSWEPT_COUNT_UPDATES"], verbose))
     codes = [p.wait() for p, _, _ in jobs]
-    for (p, tmp, out), rc in zip(jobs, codes):
-        if rc:
-            raise subprocess.CalledProcessError(rc, p.args)
-        os.replace(tmp, out)
+    try:
+        for (p, _, _), rc in zip(jobs, codes):
+            if rc:
+                raise subprocess.CalledProcessError(rc, p.args)
+        for _, tmp, out in jobs:
+            os.replace(tmp, out)
+    finally:
+        for _, tmp, _ in jobs:
+            if os.path.exists(tmp):
+                os.remove(tmp)
     return LIB
 
 
